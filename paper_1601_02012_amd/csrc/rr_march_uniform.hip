@@ -10,16 +10,12 @@
 // chiplet's L2 sees a contiguous part of the sky) or pulled from a device
 // queue by persistent workgroups.
 #include <climits>
+#include <type_traits>
 
 #include "rr_ray.hpp"
 
 namespace rr {
 namespace {
-
-__device__ __forceinline__ int wrapi(int i, int n) {
-  i %= n;
-  return i < 0 ? i + n : i;
-}
 
 // Vertex record at byte offset `off` of the tensor (6 components: three
 // 8-byte accesses in FP32, three 16-byte accesses in FP64).  A 32-bit offset
@@ -38,34 +34,20 @@ __device__ __forceinline__ void load_vertex(const R* __restrict__ tv, Off off, R
   }
 }
 
-// Q_v = P : T_v for the vertex record at byte offset off.
-template <typename R, typename Off>
-__device__ __forceinline__ R project(const R* __restrict__ tv, Off off, const R* P) {
-  R t[6];
-  load_vertex<R, Off>(tv, off, t);
-  R acc = P[0] * t[0];
-#pragma unroll
-  for (int c = 1; c < 6; ++c) acc = fma(P[c], t[c], acc);
-  return acc;
-}
-
 // Integrand modes: the tidal tensor with the trilinear integral, the tidal
 // tensor at cell centres (NGP), Method A's (c delta, grad Phi) fields, the
 // tidal tensor against the two source-distance moments chi and chi^2, and a
 // vertex scalar with a constant kernel (ISW).
 constexpr int kTidal = 0, kNgp = 1, kMethodA = 2, kSources = 3, kScalar = 4;
 
-// Corner value(s) of the record at `off`: Q = P : T (tidal modes),
+// The record at byte offset `off` and its value(s): Q = P : T (tidal modes),
 // (c delta, n . grad Phi) with P[0..2] = n (Method A), or the scalar (ISW).
 template <typename R, typename Off, int kMode>
-__device__ __forceinline__ void corner_value(const R* __restrict__ tv, Off off, const R* P, R& q,
-                                             R& q2) {
+__device__ __forceinline__ void load_record(const R* __restrict__ tv, Off off, R* t) {
+  const char* b = reinterpret_cast<const char*>(tv) + (uint64_t)off;
   if constexpr (kMode == kScalar) {
-    q = *reinterpret_cast<const R*>(reinterpret_cast<const char*>(tv) + (uint64_t)off);
-    q2 = (R)0;
+    t[0] = *reinterpret_cast<const R*>(b);
   } else if constexpr (kMode == kMethodA) {
-    const char* b = reinterpret_cast<const char*>(tv) + (uint64_t)off;
-    R t[4];
     if constexpr (sizeof(R) == 4) {
       const float4 x = *reinterpret_cast<const float4*>(b);
       t[0] = x.x; t[1] = x.y; t[2] = x.z; t[3] = x.w;
@@ -74,94 +56,168 @@ __device__ __forceinline__ void corner_value(const R* __restrict__ tv, Off off, 
       const double2 x = p[0], y = p[1];
       t[0] = x.x; t[1] = x.y; t[2] = y.x; t[3] = y.y;
     }
+  } else {
+    load_vertex<R, Off>(tv, off, t);
+  }
+}
+template <typename R, int kMode>
+__device__ __forceinline__ void record_value(const R* t, const R* P, R& q, R& q2) {
+  q2 = (R)0;
+  if constexpr (kMode == kScalar) {
+    q = t[0];
+  } else if constexpr (kMode == kMethodA) {
     q = t[0];
     q2 = fma(P[2], t[3], fma(P[1], t[2], P[0] * t[1]));
   } else {
-    q = project<R, Off>(tv, off, P);
-    q2 = (R)0;
-  }
-}
-
-// All eight corners (c = b0 + 2 b1 + 4 b2), loaded in two halves so that at
-// most four vertex records are in flight: this path runs only at the start of
-// a ray and after edge or vertex crossings, and must not set the register
-// budget of the whole loop.
-template <typename R, typename Off, int kMode>
-__device__ __forceinline__ void load_corners(const R* __restrict__ tv, Off base, const Off* dX,
-                                             const R* P, R* q, R* q2) {
-  const Off v2 = base + dX[1];
-  corner_value<R, Off, kMode>(tv, base, P, q[0], q2[0]);
-  corner_value<R, Off, kMode>(tv, base + dX[0], P, q[1], q2[1]);
-  corner_value<R, Off, kMode>(tv, v2, P, q[2], q2[2]);
-  corner_value<R, Off, kMode>(tv, v2 + dX[0], P, q[3], q2[3]);
-  __builtin_amdgcn_sched_barrier(0);
-  const Off v4 = base + dX[2];
-  const Off v6 = v4 + dX[1];
-  corner_value<R, Off, kMode>(tv, v4, P, q[4], q2[4]);
-  corner_value<R, Off, kMode>(tv, v4 + dX[0], P, q[5], q2[5]);
-  corner_value<R, Off, kMode>(tv, v6, P, q[6], q2[6]);
-  corner_value<R, Off, kMode>(tv, v6 + dX[0], P, q[7], q2[7]);
-}
-
-// One face crossed along axis k (one-hot k0, k1, k2 = neither): the four
-// values of that face move to the entry face, the four of the new exit face
-// F_j (j = i_a + 2 i_b over the two other axes a < b) come in (Method A's two
-// corner sets; the tidal path writes the same selects inline).  The selects
-// operate on register values: the empty asm statements keep the compiler
-// from turning a select of two array elements into an indexed load, which
-// would move the array to LDS.
-template <typename R>
-__device__ __forceinline__ void shift_face(R* q, bool k0, bool k1, R F0, R F1, R F2, R F3) {
-  R a[8];
+    R acc = P[0] * t[0];
 #pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    a[c] = q[c];
-    asm volatile("" : "+v"(a[c]));
+    for (int c = 1; c < 6; ++c) acc = fma(P[c], t[c], acc);
+    q = acc;
   }
-  const R n0 = k0 ? a[1] : (k1 ? a[2] : a[4]);
-  const R n1 = k0 ? F0 : (k1 ? a[3] : a[5]);
-  const R n2 = k0 ? a[3] : (k1 ? F0 : a[6]);
-  const R n3 = k0 || k1 ? F1 : a[7];
-  const R n4 = k0 ? a[5] : (k1 ? a[6] : F0);
-  const R n5 = k0 ? F2 : (k1 ? a[7] : F1);
-  const R n6 = k0 ? a[7] : F2;
-  q[0] = n0; q[1] = n1; q[2] = n2; q[3] = n3;
-  q[4] = n4; q[5] = n5; q[6] = n6; q[7] = F3;
+}
+template <typename R, typename Off, int kMode>
+__device__ __forceinline__ R point_value(const R* __restrict__ tv, Off off, const R* P) {
+  R t[6], q, q2;
+  load_record<R, Off, kMode>(tv, off, t);
+  record_value<R, kMode>(t, P, q, q2);
+  return q;
+}
+
+// Records loaded ahead of an integral are not touched before it is done: an
+// empty statement takes the sum and hands the loaded words on, so that the
+// compiler neither waits for the loads early nor moves the integral past them.
+template <int kWords, typename R>
+__device__ __forceinline__ void after_sum(R* t, R sum) {
+#pragma unroll
+  for (int c = 0; c < kWords; ++c) asm volatile("" : "+v"(t[c]) : "v"(sum));
+}
+
+// The records of a face's corners c = i_a + 2 i_b (w0 the offset of corner 0,
+// da and db the steps along its two axes), loaded ahead of their use.
+template <typename R, typename Off, int kMode>
+struct FaceRecords {
+  static constexpr int kWords = kMode == 2 ? 4 : (kMode == 4 ? 1 : 6);
+  R t[4][kWords];
+  __device__ __forceinline__ void load(const R* __restrict__ tv, Off w0, Off da, Off db) {
+    const Off w1 = w0 + da;
+    load_record<R, Off, kMode>(tv, w0, t[0]);
+    load_record<R, Off, kMode>(tv, w1, t[1]);
+    load_record<R, Off, kMode>(tv, w0 + db, t[2]);
+    load_record<R, Off, kMode>(tv, w1 + db, t[3]);
+  }
+  __device__ __forceinline__ void hold(R sum) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) after_sum<kWords>(t[c], sum);
+  }
+  // their values (one set, or Method A's two)
+  __device__ __forceinline__ void project(const R* P, R* f, R* f2) const {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) record_value<R, kMode>(t[c], P, f[c], f2[c]);
+  }
+};
+template <typename R, typename Off, int kMode>
+__device__ __forceinline__ void load_face(const R* __restrict__ tv, Off w0, Off da, Off db,
+                                          const R* P, R* f, R* f2) {
+  FaceRecords<R, Off, kMode> r;
+  r.load(tv, w0, da, db);
+  r.project(P, f, f2);
+}
+
+// The same four corners for a quad of lanes that share the face (FP32): lane i
+// of the quad has loaded the record of corner i, and v_mfma_f32_4x4x1_16b
+// (sixteen 4 x 4 outer products, one per quad) accumulates over the
+// components f[i] = sum_c T_c(lane i) P_c(own lane): the rounding of the fma
+// chain in corner_value, component by component, with a quarter of its loads.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+template <int kMode>
+__device__ __forceinline__ void project_quad(const float* t, const float* P, float* f,
+                                             float* f2) {
+  const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+  f32x4 d;
+  if constexpr (kMode == kScalar) {
+    d = __builtin_amdgcn_mfma_f32_4x4x1f32(t[0], 1.0f, zero, 0, 0, 0);
+  } else if constexpr (kMode == kMethodA) {
+    d = __builtin_amdgcn_mfma_f32_4x4x1f32(t[0], 1.0f, zero, 0, 0, 0);
+    f32x4 g = zero;
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      g = __builtin_amdgcn_mfma_f32_4x4x1f32(t[c + 1], P[c], g, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f2[i] = g[i];
+  } else {
+    d = zero;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) d = __builtin_amdgcn_mfma_f32_4x4x1f32(t[c], P[c], d, 0, 0, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) f[i] = d[i];
+}
+
+// x of lane 0 of the quad.
+__device__ __forceinline__ uint32_t quad_first(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x00, 0xf, 0xf, false);
+}
+__device__ __forceinline__ uint64_t quad_first(uint64_t x) {
+  return ((uint64_t)quad_first((uint32_t)(x >> 32)) << 32) | quad_first((uint32_t)x);
 }
 
 // One ray, in the ray's own frame: along each axis, corner bit 0 is the
 // vertex layer of the face the ray enters through and bit 1 the layer of the
 // face it leaves through, and the local coordinate f runs from 0 (entry face)
-// to 1 (exit face).  A crossing of one face then keeps the four projected
-// corner values of that face (they become the entry face of the next cell)
-// and loads only the four of the new exit face; a crossing through an edge or
-// a vertex reloads all eight.
+// to 1 (exit face).  The lattice axes are relabelled cyclically so that axis 2
+// is the one the tile's rays run along (kz: the largest component of the
+// tile's first direction); a cell's corners are its entry face E and its exit
+// face X on that axis.  A crossing of one face keeps the four projected corner
+// values of that face (they become the entry face of the next cell) and loads
+// only the four of the new exit face; a crossing through an edge or a vertex
+// reloads all eight.
 //
 // Per axis the lane keeps, in FP64, the crossing parameter of the exit plane
 // (f = 1 - |n_a| (chi - t_exit) inside the slab) and its reciprocal
-// direction, and as integers the exit plane's lattice coordinate and the
-// wrapped index of the exit vertex layer; the cell's entry corner is one byte
-// offset into the vertex array (32 bit when the tensor is below 4 GiB), with
-// per-axis steps to the exit layer (modular arithmetic).
+// direction, the exit plane's lattice coordinate, and the byte offsets of the
+// wrapped entry and exit vertex layers (32 bit when the tensor is below
+// 4 GiB): a corner's offset is the sum of one of them per axis.
+//
+// Most cells of a bundle are entered and left through faces of axis 2.  While
+// every lane of the wavefront is about to leave its cell that way, the march
+// runs a short loop of its own: no exit selection, no stepping of the other
+// axes, the entry face's bilinear coefficients and the value at the entry
+// point carried over from the last cell, and (FP32) one record per lane
+// instead of four, shared within quads and projected on the matrix cores.
+// Between runs every lane crosses one face at a time with the loads of the new
+// face in flight during the integral; what neither covers (edges, ends of the
+// window, sources, open grids, debug outputs, crossing limits) takes the cell
+// of any kind at the bottom.  All three round a piece alike, so a ray's result
+// depends neither on its neighbours nor on the launch.
+//
+// What bounds it is VALU issue, with the address path of the gathers close
+// behind (an FP32 operation on vector registers takes a SIMD 2.5 clocks, an
+// FP64 one, a compare, a select, an integer minimum or a conversion 4.3, the
+// 4 x 4 matrix instruction 8.6): 120 VALU instructions per crossing and
+// wavefront (69 in the run, 175 in a step between runs) against 206 for one
+// loop over cells of any kind with a three-point Gauss rule; address unit 80 %
+// busy.  512^3, 2048^2 rays over 5 degrees: 0.88 ms per segment (1.12 before).
+// Keeping the wavefront in one layer of axis 2 (lanes that leave sideways
+// cross first, the others wait) costs more than it saves: 150 VALU, 0.97 ms.
 template <typename R, bool kDebug, typename Off, int kMode, bool kPass>
 __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const DevBundle& B,
-                          int64_t ray) {
+                          int64_t ray, bool own) {
   const int64_t out = B.ray_offset + ray;
-  const double d[3] = {B.dir[3 * ray + 0], B.dir[3 * ray + 1], B.dir[3 * ray + 2]};
+  const double dir[3] = {B.dir[3 * ray + 0], B.dir[3 * ray + 1], B.dir[3 * ray + 2]};
   // Only unit directions are traced: that bounds the number of crossings by
   // the chi window validated on the host, so every lane terminates.
-  const double nrm2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+  const double nrm2 = dir[0] * dir[0] + dir[1] * dir[1] + dir[2] * dir[2];
   if (!(fabs(nrm2 - 1.0) <= 1e-9)) {
-    if (a.status) a.status[out] = RR_RAY_BAD_DIRECTION;
+    if (a.status && own) a.status[out] = RR_RAY_BAD_DIRECTION;
     return;
   }
   R P[6];
   if constexpr (kMode == kMethodA || kMode == kScalar) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) P[c] = (R)d[c];
+    for (int c = 0; c < 3; ++c) P[c] = (R)dir[c];
   } else {
     double Pd[6];
-    projection(a.quantity, d[0], d[1], d[2], Pd);
+    projection(a.quantity, dir[0], dir[1], dir[2], Pd);
 #pragma unroll
     for (int c = 0; c < 6; ++c) P[c] = (R)Pd[c];
   }
@@ -169,7 +225,19 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
   const int n = a.n;
   constexpr Off kRec =
       (Off)((kMode == kMethodA ? 4 : (kMode == kScalar ? 1 : 6)) * sizeof(R));  // bytes per record
-  const Off stride[3] = {kRec, kRec * (Off)n, kRec * (Off)n * (Off)n};
+  // axis 2 of the frame is lattice axis kz, axes 0 and 1 the two after it
+  int kz = fabs(dir[0]) > fabs(dir[2]) ? 0 : 2;
+  kz = fabs(dir[1]) > fmax(fabs(dir[0]), fabs(dir[2])) ? 1 : kz;
+  kz = __builtin_amdgcn_readfirstlane(kz);
+  const double d[3] = {kz == 2 ? dir[0] : (kz == 0 ? dir[1] : dir[2]),
+                       kz == 2 ? dir[1] : (kz == 0 ? dir[2] : dir[0]),
+                       kz == 2 ? dir[2] : (kz == 0 ? dir[0] : dir[1])};
+  const double o[3] = {kz == 2 ? a.o[0] : (kz == 0 ? a.o[1] : a.o[2]),
+                       kz == 2 ? a.o[1] : (kz == 0 ? a.o[2] : a.o[0]),
+                       kz == 2 ? a.o[2] : (kz == 0 ? a.o[0] : a.o[1])};
+  const Off sx = kRec, sy = kRec * (Off)n, sz = kRec * (Off)n * (Off)n;
+  const Off stride[3] = {kz == 2 ? sx : (kz == 0 ? sy : sz), kz == 2 ? sy : (kz == 0 ? sz : sx),
+                         kz == 2 ? sz : (kz == 0 ? sx : sy)};
   const double lo = B.chi_lo;
   double chiA = B.chi_hi;
   // a later pass resumes on the face where the last one stopped
@@ -181,34 +249,30 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
   }
   double r[3], te[3];
   R absd[3];         // f(chi) = 1 - absd (chi - t_exit)
-  int px[3];         // lattice coordinate of the exit plane (unwrapped, replicated box)
-  int xl[3];         // exit vertex layer, wrapped into [0, n)
-  Off base = 0;      // byte offset of the corner on all three entry layers
-  Off dX[3];         // byte step from the entry to the exit layer
+  double pp[3];      // lattice coordinate of the exit plane (unwrapped, replicated box)
+  Off oE[3], oX[3];  // byte offsets of the entry and the exit vertex layer, wrapped into [0, n)
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     r[k] = (d[k] != 0.0) ? 1.0 / d[k] : 0.0;
-    const int m = start_slab(a.o[k], d[k], r[k], chiA, 1.0);
+    const int m = start_slab(o[k], d[k], r[k], chiA, 1.0);
     // n_a > 0: the march runs down the lattice, leaving through plane m;
     // otherwise up, leaving through plane m + 1 (never reached if n_a = 0)
-    px[k] = d[k] > 0.0 ? m : m + 1;
+    pp[k] = (double)(d[k] > 0.0 ? m : m + 1);
     if (d[k] != 0.0) {
-      te[k] = tplane((double)px[k], a.o[k], r[k]);
+      te[k] = tplane(pp[k], o[k], r[k]);
       absd[k] = (R)fabs(d[k]);
     } else {
       // never crossed: a slope of 1e-30 with an exit parameter (1 - f) 1e30
       // below reproduces the fixed coordinate f = o~ - m to rounding, and the
       // parameter is never the largest (chi_lo >= 0)
-      te[k] = -(1.0 - (a.o[k] - (double)m)) * 1e30;
+      te[k] = -(1.0 - (o[k] - (double)m)) * 1e30;
       absd[k] = (R)1e-30;
     }
     int lm = m % n;
     lm = lm < 0 ? lm + n : lm;                       // layer of plane m
     const int lp = lm + 1 == n ? 0 : lm + 1;         // layer of plane m + 1
-    const int el = d[k] > 0.0 ? lp : lm;
-    xl[k] = d[k] > 0.0 ? lm : lp;
-    base += (Off)el * stride[k];
-    dX[k] = (Off)xl[k] * stride[k] - (Off)el * stride[k];
+    oE[k] = (Off)(d[k] > 0.0 ? lp : lm) * stride[k];
+    oX[k] = (Off)(d[k] > 0.0 ? lm : lp) * stride[k];
   }
   R fA[3];
 #pragma unroll
@@ -216,16 +280,44 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
     fA[k] = (R)1 - absd[k] * (R)(chiA - te[k]);
     // on the entry face (a resumed ray, or a window that starts on a face)
     // the coordinate is 0, as when the march steps across that face
-    if (kPass && d[k] != 0.0 &&
-        chiA == tplane((double)(d[k] > 0.0 ? px[k] + 1 : px[k] - 1), a.o[k], r[k]))
+    if (kPass && d[k] != 0.0 && chiA == tplane(d[k] > 0.0 ? pp[k] + 1.0 : pp[k] - 1.0, o[k], r[k]))
       fA[k] = (R)0;
   }
+  // axis 2 marched as a countdown: its exit layer's offset is (mx ^ up) + cx
+  // with mx one stride less at every crossing and the last layer after 0
+  const Off span2 = (Off)(n - 1) * stride[2];
+  const bool down2 = d[2] > 0.0;
+  const Off up = down2 ? (Off)0 : ~(Off)0;
+  const Off cx = down2 ? (Off)0 : span2 + (Off)1;
+  const double step2 = down2 ? -1.0 : 1.0;
 
-  R q[8], q2[8];  // corner values (q2: Method A's gradient term), c = b0 + 2 b1 + 4 b2
-  if constexpr (kMode != kNgp) load_corners<R, Off, kMode>(tv, base, dX, P, q, q2);
+  constexpr bool kTwo = kMode == kMethodA;   // a second set of corner values (n . grad Phi)
+  // corner values c = i_0 + 2 i_1 of the entry and the exit face of axis 2
+  // (2: Method A's gradient set)
+  R E[4], X[4], E2[4], X2[4];
+  // all eight corners, in two halves so that at most four records are in
+  // flight: this must not set the register budget of the whole march
+  auto load_cell = [&] {
+    const Off da = oX[0] - oE[0], db = oX[1] - oE[1];
+    load_face<R, Off, kMode>(tv, oE[0] + oE[1] + oE[2], da, db, P, E, E2);
+    __builtin_amdgcn_sched_barrier(0);
+    load_face<R, Off, kMode>(tv, oE[0] + oE[1] + oX[2], da, db, P, X, X2);
+  };
+  if constexpr (kMode != kNgp) load_cell();
 
-  const R inv_chis = (R)(1.0 / B.chi_s);
-  const R scale = (R)a.kappa_scale;
+  const double chi_s = B.chi_s;
+  // what multiplies a piece's integral (the forms give 12 times it, the
+  // kernels of the lensing integrands chi_s times theirs).  FP32 keeps the part
+  // that its rounding leaves out, which would be one relative error of up to
+  // 6e-8 common to all pieces.
+  const double form = kMode == kNgp ? 1.0 : 1.0 / 12.0;
+  const double factor = kMode == kScalar || kMode == kSources ? a.kappa_scale * form
+                                                              : a.kappa_scale * form / chi_s;
+  const R scale = (R)factor, scale_rest = (R)(factor - (double)scale);
+  auto scaled = [&](R x) {
+    if constexpr (sizeof(R) == 4) return fma(x, scale, x * scale_rest);
+    else return x * scale;
+  };
   R sum;
   float comp = 0.0f;
   // source-distance moments: (sum, comp) integrate chi Q, (sum2, comp2)
@@ -255,14 +347,254 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
   int64_t count = 0;
   int32_t st = RR_RAY_OK;
   const int64_t maxc = a.max_crossings > 0 ? a.max_crossings : INT64_MAX;
+  // the run along axis 2 keeps no count, hash or domain test
+  const bool may_run = !kDebug && !a.open && a.max_crossings <= 0;
+
+  // the kernel at chi: g times chi_s (tidal), chi (sources), both g and
+  // dg/dchi times chi_s (Method A)
+  auto kernel = [&](double chi, R& k0, R& k1) {
+    const R c = (R)chi;
+    k0 = c;
+    k1 = 0;
+    if constexpr (kMode == kTidal || kMode == kMethodA) {
+      const R rest = (R)(chi_s - chi);
+      k0 = c * rest;
+      if constexpr (kMode == kMethodA) k1 = rest - c;
+    }
+  };
+  // adds the piece of length L with the form q (q2: the gradient's), its
+  // kernel values at both ends
+  auto add_piece = [&](const PieceForm<R>& q, const PieceForm<R>& q2, R L, R gA, R gB, R hA, R hB,
+                       R surface) {
+    R ic, ic2 = 0;
+    if constexpr (kMode == kScalar) {
+      ic = integrate_constant(q) * scaled(L);
+    } else if constexpr (kMode == kSources) {
+      // the moments' kernels chi and chi^2 (curvature -L^2)
+      const R Ls = scaled(L);
+      ic = integrate_form(q, gA, gB, (R)0) * Ls;
+      ic2 = integrate_form(q, gA * gA, gB * gB, -(L * L)) * Ls;
+    } else {
+      R s = integrate_form(q, gA, gB, L * L);
+      if constexpr (kMode == kMethodA) s += integrate_form(q2, hA, hB, (R)0);
+      ic = scaled(fma(s, L, surface));
+    }
+    if constexpr (sizeof(R) == 4) {
+      kahan_add(sum, comp, ic);
+      if constexpr (kMode == kSources) kahan_add(sum2, comp2, ic2);
+    } else {
+      sum += ic;
+      if constexpr (kMode == kSources) sum2 += ic2;
+    }
+  };
+  // Eq. (Iclensing_ngp): the cell-centre value times the integral of g over
+  // the piece, L (g(mid) - L^2 / (12 chi_s)) with g(chi) = chi (chi_s - chi) / chi_s
+  auto add_ngp = [&](R Qc, double chiB, R L) {
+    const double mid = chiB + 0.5 * (chiA - chiB);
+    const R gm = (R)mid * (R)(chi_s - mid) - L * L * (R)(1.0 / 12.0);
+    const R ic = Qc * scaled(gm * L);
+    if constexpr (sizeof(R) == 4) kahan_add(sum, comp, ic);
+    else sum += ic;
+  };
+  R gA, hA;   // kernel values at chi_A
+  kernel(chiA, gA, hA);
+
+  // steps axis k: the exit layer becomes the entry layer, the next layer
+  // along the march the exit layer
+  auto next_layer = [&](int k) {
+    const bool down = r[k] > 0.0;
+    const Off top = (Off)(n - 1) * stride[k];
+    pp[k] += down ? -1.0 : 1.0;
+    te[k] = tplane(pp[k], o[k], r[k]);
+    oE[k] = oX[k];
+    const Off wrap_at = down ? (Off)0 : top, wrap_to = down ? top : (Off)0;
+    const Off next = down ? oX[k] - stride[k] : oX[k] + stride[k];
+    oX[k] = oX[k] == wrap_at ? wrap_to : next;
+  };
+  // offset of the record of the cell: the lower vertex layer on every axis
+  auto cell_offset = [&] {
+    Off low = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) low += r[k] > 0.0 ? oX[k] : oE[k];
+    return low;
+  };
 
   for (;;) {
+    // the walk stops at chi_lo, or at the next source distance above it; a
+    // pass also before its boundary
+    double stop = lo;
+    if constexpr (kMode == kSources) stop = src_j >= lo ? src_j : lo;
+    // (Method A's first piece carries a surface term)
+    const bool go = may_run && (!kTwo || chiA < B.chi_hi);
+    const unsigned long long all = __ballot(1);
+    double halt = stop;
+    if constexpr (kPass) halt = fmax(stop, a.pause_chi);
+    while (__ballot(go) == all) {
+      const double side = fmax(te[0], te[1]);
+      const double lim = fmax(side, halt);
+      const Off w01 = oE[0] + oE[1];
+      // one record per lane: all 64 lanes march (matrix instructions ignore
+      // the execution mask), and the four lanes of every quad are in one cell
+      // and share its frame
+      bool run = __ballot(te[2] > lim) == all;
+      if constexpr (sizeof(R) == 4 && kMode != kNgp) {
+        const Off w = w01 + oX[2], w2 = oX[0] + oX[1];
+        run = run && (__ballot(quad_first(w) == w) & __ballot(quad_first(w2) == w2)) == ~0ull;
+      }
+      if (run) {
+        // ---- every lane leaves its cell through axis 2 alone
+        if constexpr (kMode == kNgp) {
+          do {
+            const R Qc = point_value<R, Off, kMode>(tv, cell_offset(), P);
+            add_ngp(Qc, te[2], (R)(chiA - te[2]));
+            chiA = te[2];
+            next_layer(2);
+          } while (__ballot(te[2] > lim) == all);
+        } else {
+          const Off da = oX[0] - oE[0], db = oX[1] - oE[1];
+          const Off off = w01 + ((threadIdx.x & 1) ? da : (Off)0) + ((threadIdx.x & 2) ? db : (Off)0);
+          // countdown of the exit layer: its offset is (mx ^ up) + cx
+          Off mx = (oX[2] - cx) ^ up;
+          Face<R> fE(E), fX(X), gE, gX;
+          R u0 = form_start(fE, fX, fA), v0 = 0;   // values at the entry point
+          if constexpr (kTwo) {
+            gE = Face<R>(E2);
+            gX = Face<R>(X2);
+            v0 = form_start(gE, gX, fA);
+          }
+          // one cell: entry face e, exit face x; the next exit face replaces e.
+          // first: the entry point may lie inside the cell (zA > 0)
+          auto step = [&](Face<R>& e, Face<R>& x, Face<R>& e2, Face<R>& x2, auto first) {
+            mx = mx - stride[2] < span2 ? mx - stride[2] : span2;
+            const Off nx = (mx ^ up) + cx;
+            FaceRecords<R, Off, kMode> rec;
+            if constexpr (sizeof(R) == 4)
+              load_record<R, Off, kMode>(tv, off + nx, rec.t[0]);
+            else
+              rec.load(tv, w01 + nx, da, db);
+            __builtin_amdgcn_sched_barrier(0);   // in flight during the integral
+            const double chiB = te[2];
+            const R L = (R)(chiA - chiB);
+            const R xB = (R)1 - absd[0] * (R)(chiB - te[0]);
+            const R yB = (R)1 - absd[1] * (R)(chiB - te[1]);
+            R gB, hB;
+            kernel(chiB, gB, hB);
+            PieceForm<R> q, q2;
+            if constexpr (first.value) {
+              q = form_out(e, x, u0, fA[0], fA[1], fA[2], xB, yB);
+              if constexpr (kTwo) q2 = form_out(e2, x2, v0, fA[0], fA[1], fA[2], xB, yB);
+            } else {
+              q = form_through(e, x, u0, fA[0], fA[1], xB, yB);
+              if constexpr (kTwo) q2 = form_through(e2, x2, v0, fA[0], fA[1], xB, yB);
+            }
+            add_piece(q, q2, L, gA, gB, hA, hB, (R)0);
+            u0 = q.u1;
+            if constexpr (kTwo) v0 = q2.u1;
+            gA = gB;
+            hA = hB;
+            fA[0] = xB;
+            fA[1] = yB;
+            chiA = chiB;
+            pp[2] += step2;
+            te[2] = tplane(pp[2], o[2], r[2]);
+            if constexpr (sizeof(R) == 4) after_sum<rec.kWords>(rec.t[0], sum);
+            else rec.hold(sum);
+            R nf[4], nf2[4];
+            if constexpr (sizeof(R) == 4)
+              project_quad<kMode>(rec.t[0], P, nf, nf2);
+            else
+              rec.project(P, nf, nf2);
+            e = Face<R>(nf);
+            if constexpr (kTwo) e2 = Face<R>(nf2);
+          };
+          using no = std::false_type;
+          step(fE, fX, gE, gX, std::true_type{});
+          bool odd = true;
+          for (;;) {
+            if (__ballot(te[2] > lim) != all) break;
+            step(fX, fE, gX, gE, no{});
+            odd = false;
+            if (__ballot(te[2] > lim) != all) break;
+            step(fE, fX, gE, gX, no{});
+            odd = true;
+          }
+          // after an odd number of cells the roles of the two faces are swapped
+          if (odd) {
+            swap_faces(fE, fX);
+            if constexpr (kTwo) swap_faces(gE, gX);
+          }
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            E[c] = fE.q[c];
+            X[c] = fX.q[c];
+            if constexpr (kTwo) {
+              E2[c] = gE.q[c];
+              X2[c] = gX.q[c];
+            }
+          }
+          oX[2] = (mx ^ up) + cx;
+          // the entry layer is the one before it
+          const Off back = mx == span2 ? (Off)0 : mx + stride[2];
+          oE[2] = (back ^ up) + cx;
+        }
+        fA[2] = (R)0;
+      }
+      // ---- every lane leaves its cell through one face (m0, m1: the lanes
+      // that do through axis 0 or 1, the others through axis 2)
+      const unsigned long long m2 = __ballot(te[2] > lim);
+      const unsigned long long ms =
+          __ballot(side > te[2]) & __ballot(side > halt) & __ballot(te[0] != te[1]);
+      if ((m2 | ms) != all) break;
+      const double chiB = fmax(te[2], side);
+      const unsigned long long m0 = ms & __ballot(te[0] > te[1]), m1 = ms & ~m0;
+      R fB[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) fB[k] = (R)1 - absd[k] * (R)(chiB - te[k]);
+      R ngp = 0;   // NGP: the value of the cell being left
+      if constexpr (kMode == kNgp) ngp = point_value<R, Off, kMode>(tv, cell_offset(), P);
+      const bool k2 = te[2] == chiB, k0 = te[0] == chiB, k1 = te[1] == chiB;
+      if (k2) next_layer(2);
+      if (k0) next_layer(0);
+      if (k1) next_layer(1);
+      // the four records of the new exit face, in flight during the integral
+      FaceRecords<R, Off, kMode> rec;
+      if constexpr (kMode != kNgp) {
+        const Off w0 = (k0 ? oX[0] : oE[0]) + (k1 ? oX[1] : oE[1]) + (k2 ? oX[2] : oE[2]);
+        rec.load(tv, w0, k0 ? oX[1] - oE[1] : oX[0] - oE[0], k2 ? oX[1] - oE[1] : oX[2] - oE[2]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      const R L = (R)(chiA - chiB);
+      R gB, hB;
+      kernel(chiB, gB, hB);
+      if constexpr (kMode == kNgp) {
+        add_ngp(ngp, chiB, L);
+      } else {
+        const PieceForm<R> q = form_general(Face<R>(E), Face<R>(X), fA, fB);
+        PieceForm<R> q2 = q;
+        if constexpr (kTwo) q2 = form_general(Face<R>(E2), Face<R>(X2), fA, fB);
+        add_piece(q, q2, L, gA, gB, hA, hB, (R)0);
+      }
+      gA = gB;
+      hA = hB;
+      chiA = chiB;
+      fA[0] = pick(m0, (R)0, fB[0]);
+      fA[1] = pick(m1, (R)0, fB[1]);
+      fA[2] = pick(m0 | m1, fB[2], (R)0);
+      if constexpr (kMode != kNgp) {
+        rec.hold(sum);
+        R F[4], F2[4];
+        rec.project(P, F, F2);
+        shift_face<R>(E, X, m0, m1, F);
+        if constexpr (kTwo) shift_face<R>(E2, X2, m0, m1, F2);
+      }
+    }
+    // ---- one cell of any kind
     if (a.open) {
       bool outside = false;
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        const int m = r[k] > 0.0 ? px[k] : px[k] - 1;
-        outside |= m < 2 || m > n - 3;
+        const double m = r[k] > 0.0 ? pp[k] : pp[k] - 1.0;
+        outside |= m < 2.0 || m > (double)(n - 3);
       }
       if (outside) {
         st = RR_RAY_OUT_OF_DOMAIN;
@@ -276,13 +608,9 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
       st = RR_RAY_MAX_STEPS;
       break;
     }
-    // exit point: chi_B = max(chi_lo, t_exit,x, t_exit,y, t_exit,z), ties keep the earlier
-    // (the next source distance takes the place of chi_lo when it lies above it)
-    double chiB = lo;
-    if constexpr (kMode == kSources) chiB = src_j >= lo ? src_j : lo;
-    chiB = te[0] > chiB ? te[0] : chiB;
-    chiB = te[1] > chiB ? te[1] : chiB;
-    chiB = te[2] > chiB ? te[2] : chiB;
+    // exit point: chi_B = max(chi_lo, t_exit,x, t_exit,y, t_exit,z)
+    double chiB = fmax(fmax(fmax(te[0], te[1]), te[2]), stop);
+    if constexpr (kDebug) chiB = chiB == lo ? lo : chiB;   // the bits of chi_lo itself
     bool stepped[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) stepped[k] = te[k] == chiB;
@@ -292,60 +620,30 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
 #pragma unroll
     for (int k = 0; k < 3; ++k) fB[k] = (R)1 - absd[k] * (R)(chiB - te[k]);
     const R L = (R)(chiA - chiB);
-    R ic, ic2 = 0;
-    if constexpr (kMode == kSources) {
-      R ma, mb;
-      cell_moments<R>(q, fA, fB, L, (R)chiB, ma, mb);
-      ic = ma * scale;
-      ic2 = mb * scale;
-    } else if constexpr (kMode == kScalar) {
-      ic = cell_integral_scalar<R>(q, fA, fB, L) * scale;
-    } else if constexpr (kMode == kMethodA) {
-      // Eq. (kappa2): c delta against g, n . grad Phi against dg/dchi, and the
-      // step's surface term -[g n . grad Phi] at its first and last point
-      R s = cell_integral_a<R>(q, q2, fA, fB, L, (R)chiB, (R)(B.chi_s - chiB), inv_chis);
-      const bool first = count == 0 && chiA == B.chi_hi, last = chiB == lo;
-      if (first || last) {
-        R dq[4];
-        dq[0] = q2[1] - q2[0]; dq[1] = q2[3] - q2[2]; dq[2] = q2[5] - q2[4]; dq[3] = q2[7] - q2[6];
-        if (first) {
-          const R g = (R)chiA * (R)(B.chi_s - chiA) * inv_chis;
-          s -= g * trilerp<R>(q2, dq, fA[0], fA[1], fA[2]);
-        }
-        if (last) {
-          const R g = (R)chiB * (R)(B.chi_s - chiB) * inv_chis;
-          s += g * trilerp<R>(q2, dq, fB[0], fB[1], fB[2]);
-        }
+    R gB, hB;
+    kernel(chiB, gB, hB);
+    if constexpr (kMode == kNgp) {
+      add_ngp(point_value<R, Off, kMode>(tv, cell_offset(), P), chiB, L);
+    } else {
+      const PieceForm<R> q = form_general(Face<R>(E), Face<R>(X), fA, fB);
+      PieceForm<R> q2 = q;
+      R surface = 0;
+      if constexpr (kTwo) {
+        // Eq. (kappa2): c delta against g, n . grad Phi against dg/dchi, and the
+        // step's surface term -[g n . grad Phi] at its first and last point
+        q2 = form_general(Face<R>(E2), Face<R>(X2), fA, fB);
+        if (chiA == B.chi_hi) surface -= (R)12 * gA * q2.u0;
+        if (chiB == lo) surface += (R)12 * gB * q2.u1;
       }
-      ic = s * scale;
-    } else if constexpr (kMode == kNgp) {
-      // Eq. (Iclensing_ngp): the cell-centre value times the integral of g over
-      // the piece, L (g(mid) - L^2 / (12 chi_s)) with g(chi) = chi (chi_s - chi) / chi_s
-      Off cellv = base;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) cellv += r[k] > 0.0 ? dX[k] : (Off)0;
-      const R Qc = project<R, Off>(tv, cellv, P);
-      const double mid = chiB + 0.5 * (chiA - chiB);
-      const R gm = (R)mid * (R)(B.chi_s - mid) - L * L * (R)(1.0 / 12.0);
-      ic = Qc * (gm * L * inv_chis) * scale;
-    } else {
-      ic = cell_integral<R>(q, fA, fB, L, (R)chiB, (R)(B.chi_s - chiB), inv_chis) * scale;
+      add_piece(q, q2, L, gA, gB, hA, hB, surface);
     }
-    if constexpr (sizeof(R) == 4) {
-      kahan_add(sum, comp, ic);
-      if constexpr (kMode == kSources) kahan_add(sum2, comp2, ic2);
-    } else {
-      sum += ic;
-      if constexpr (kMode == kSources) sum2 += ic2;
-    }
+    gA = gB;
+    hA = hB;
     if constexpr (kDebug) {
-      // cell id = vertex id of its lower corner: the exit layer where n_a > 0
-      Off low = base;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) low += r[k] > 0.0 ? dX[k] : (Off)0;
-      const int64_t cell = (int64_t)(low / kRec);
+      // cell id = vertex id of its lower corner
+      const int64_t cell = (int64_t)(cell_offset() / kRec);
       if (a.hash) hv = fnv_piece(hv, cell, chiA, chiB);
-      if (a.log && count < a.log_stride) {
+      if (own && a.log && count < a.log_stride) {
         LogRecord* L0 = reinterpret_cast<LogRecord*>(a.log) + out * a.log_stride + count;
         L0->cell = cell;
         L0->chi_a = chiA;
@@ -356,9 +654,11 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
     if constexpr (kMode == kSources) {
       if (src_j == chiB) {
         // hand out the two integrals accumulated since the previous stop
-        double* pc = a.pieces + (out * a.n_src + jn) * 2;
-        pc[0] = (double)sum - (double)comp;
-        pc[1] = (double)sum2 - (double)comp2;
+        if (own) {
+          double* pc = a.pieces + (out * a.n_src + jn) * 2;
+          pc[0] = (double)sum - (double)comp;
+          pc[1] = (double)sum2 - (double)comp2;
+        }
         sum = 0; comp = 0.0f; sum2 = 0; comp2 = 0.0f;
         ++jn;
         src_j = jn < a.n_src ? a.src[jn] : -1.0;
@@ -368,80 +668,39 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
       chiA = lo;
       break;
     }
-    // step every axis whose exit plane is at chi_B: the exit layer becomes
-    // the entry layer, the next layer along the march the exit layer
+    chiA = chiB;
+    // step every axis whose exit plane is at chi_B
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       fA[k] = fB[k];
       if (stepped[k]) {
         fA[k] = (R)0;
-        const bool down = r[k] > 0.0;
-        px[k] += down ? -1 : 1;
-        te[k] = tplane((double)px[k], a.o[k], r[k]);
-        base += dX[k];
-        const Off wrapstep = (Off)(n - 1) * stride[k];
-        if (down) {
-          const bool wrap = xl[k] == 0;
-          xl[k] = wrap ? n - 1 : xl[k] - 1;
-          dX[k] = wrap ? wrapstep : (Off)0 - stride[k];
-        } else {
-          const bool wrap = xl[k] == n - 1;
-          xl[k] = wrap ? 0 : xl[k] + 1;
-          dX[k] = wrap ? (Off)0 - wrapstep : stride[k];
-        }
+        next_layer(k);
       }
     }
+    if constexpr (kMode == kNgp) continue;   // one record per cell: nothing carried over
     const int n_stepped = (int)stepped[0] + (int)stepped[1] + (int)stepped[2];
-    if constexpr (kMode == kNgp) {
-      // one record per cell: nothing carried from cell to cell
-    } else if (kMode == kSources && n_stepped == 0) {
-      // stopped at a source distance inside the cell: same corners
-    } else if (n_stepped == 1) {
-      // one face crossed (axis k): keep its four values, load the new exit face,
-      // whose corners F_j (j = i_a + 2 i_b over the two other axes a < b)
+    if (kMode == kSources && n_stepped == 0) continue;   // a source inside the cell: same corners
+    if (n_stepped == 1) {
+      // one face crossed (axis k): its four values stay, the new exit face
+      // comes in, corners F_j (j = i_a + 2 i_b over the two other axes a < b)
       const bool k0 = stepped[0], k1 = stepped[1];
-      const Off dk = k0 ? dX[0] : (k1 ? dX[1] : dX[2]);
-      const Off da = k0 ? dX[1] : dX[0];
-      const Off db = k0 || k1 ? dX[2] : dX[1];
-      const Off w0 = base + dk, w1 = w0 + da;
-      if constexpr (kMode == kMethodA || kMode == kScalar) {
-        R F[4], G[4];
-        corner_value<R, Off, kMode>(tv, w0, P, F[0], G[0]);
-        corner_value<R, Off, kMode>(tv, w1, P, F[1], G[1]);
-        corner_value<R, Off, kMode>(tv, w0 + db, P, F[2], G[2]);
-        corner_value<R, Off, kMode>(tv, w1 + db, P, F[3], G[3]);
-        shift_face<R>(q, k0, k1, F[0], F[1], F[2], F[3]);
-        if constexpr (kMode == kMethodA) shift_face<R>(q2, k0, k1, G[0], G[1], G[2], G[3]);
-      } else {
-        const R F0 = project<R, Off>(tv, w0, P);
-        const R F1 = project<R, Off>(tv, w1, P);
-        const R F2 = project<R, Off>(tv, w0 + db, P);
-        const R F3 = project<R, Off>(tv, w1 + db, P);
-        if (__ballot(!k0 && !k1) == __ballot(1)) {
-          // every marching lane crossed a z face (lines of sight near the z
-          // axis): the old exit face becomes the entry face, no selects
-          q[0] = q[4]; q[1] = q[5]; q[2] = q[6]; q[3] = q[7];
-          q[4] = F0; q[5] = F1; q[6] = F2; q[7] = F3;
-          chiA = chiB;
-          continue;
-        }
-        const R n0 = k0 ? q[1] : (k1 ? q[2] : q[4]);
-        const R n1 = k0 ? F0 : (k1 ? q[3] : q[5]);
-        const R n2 = k0 ? q[3] : (k1 ? F0 : q[6]);
-        const R n3 = k0 || k1 ? F1 : q[7];
-        const R n4 = k0 ? q[5] : (k1 ? q[6] : F0);
-        const R n5 = k0 ? F2 : (k1 ? q[7] : F1);
-        const R n6 = k0 ? q[7] : F2;
-        q[0] = n0; q[1] = n1; q[2] = n2; q[3] = n3;
-        q[4] = n4; q[5] = n5; q[6] = n6; q[7] = F3;
-      }
+      const Off w0 = (k0 ? oX[0] : oE[0]) + (k1 ? oX[1] : oE[1]) +
+                     (k0 || k1 ? oE[2] : oX[2]);
+      const Off da = k0 ? oX[1] - oE[1] : oX[0] - oE[0];
+      const Off db = k0 || k1 ? oX[2] - oE[2] : oX[1] - oE[1];
+      R F[4], F2[4];
+      load_face<R, Off, kMode>(tv, w0, da, db, P, F, F2);
+      const unsigned long long m0 = __ballot(k0), m1 = __ballot(k1);
+      shift_face<R>(E, X, m0, m1, F);
+      if constexpr (kTwo) shift_face<R>(E2, X2, m0, m1, F2);
     } else {
-      load_corners<R, Off, kMode>(tv, base, dX, P, q, q2);
+      load_cell();
     }
-    chiA = chiB;
   }
   // a ray that ended without reaching chi_lo or an error stopped at a pass boundary
   const bool paused = st == RR_RAY_OK && chiA > lo;
+  if (!own) return;
   if (!(sum == sum) || sum - sum != (R)0) st = RR_RAY_NONFINITE;
   if constexpr (kMode == kSources) {
     if (!(sum2 == sum2) || sum2 - sum2 != (R)0) st = RR_RAY_NONFINITE;
@@ -471,19 +730,35 @@ __device__ __forceinline__ void run_tile(const R* __restrict__ tv, const TraceAr
   const DevBundle& B = a.bundles[b];
   int tx, ty;
   zorder_tile(tile - B.tile_begin, B.tiles_x, B.tiles_y, tx, ty);
-  const int ix = tx * 8 + (lane & 7), iy = ty * 8 + (lane >> 3);
-  if (ix < B.nx && iy < B.ny) trace_one<R, kDebug, Off, kMode, kPass>(tv, a, B, (int64_t)iy * B.nx + ix);
+  // lanes in Z order: a quad is a 2 x 2 block of rays.  At the ragged edge of
+  // a map the lanes beyond it walk the map's last ray again and write nothing,
+  // so that their quads stay whole.
+  int ix, iy;
+  zorder_lane(lane, ix, iy);
+  ix += tx * 8;
+  iy += ty * 8;
+  const bool own = ix < B.nx && iy < B.ny;
+  ix = min(ix, B.nx - 1);
+  iy = min(iy, B.ny - 1);
+  trace_one<R, kDebug, Off, kMode, kPass>(tv, a, B, (int64_t)iy * B.nx + ix, own);
+}
+
+// Wavefronts per SIMD that the register budget is held to: four (128 VGPRs)
+// for FP32 with 32-bit offsets, three where 64-bit offsets would spill more
+// under that cap; FP64 takes what it needs (three: 32 registers spilled, 24.0
+// against 16.0 ms for five 512^3 segments).  Five (96 VGPRs, 14 spilled) gained
+// nothing: 0.95 against 0.89 ms per 512^3 segment of 2048^2 rays; Method A,
+// which spills 8 at four, takes 8.4 ms for five segments against 8.8 at three.
+template <typename R, typename Off>
+constexpr int waves_per_simd() {
+  return sizeof(R) == 8 ? 1 : (sizeof(Off) == 4 ? 4 : 3);
 }
 
 // One wavefront per tile.  Workgroups are dealt round-robin to the 8 XCDs;
-// remap so that XCD x gets the x-th contiguous slice of tiles.  The FP32 loop
-// is held to 96 VGPRs (5 wavefronts per SIMD): the march waits on dependent
-// gathers, and the fifth wavefront hides more of that latency than the
-// compiler's unconstrained schedule (100 VGPRs, 4 wavefronts) gains.
+// remap so that XCD x gets the x-th contiguous slice of tiles.
 template <typename R, bool kDebug, typename Off, int kMode, bool kPass>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 5 : 1)))
-void march_uniform_kernel(const R* __restrict__ tv,
-                                                            TraceArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_simd<R, Off>())))
+void march_uniform_kernel(const R* __restrict__ tv, TraceArgs a) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int64_t nblk = gridDim.x;
@@ -502,8 +777,8 @@ void march_uniform_kernel(const R* __restrict__ tv,
 // the exit test).  The tile is the same for the 64 lanes: it (and the
 // bundle) stays scalar.
 template <typename R, bool kDebug, typename Off, int kMode, bool kPass>
-__global__ __launch_bounds__(256) void march_uniform_persistent(const R* __restrict__ tv,
-                                                                TraceArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_simd<R, Off>())))
+void march_uniform_persistent(const R* __restrict__ tv, TraceArgs a) {
   const int lane = threadIdx.x & 63;
   int q = blockIdx.x % kQueues, tried = 0;
   for (;;) {

@@ -151,33 +151,6 @@ __device__ __forceinline__ R cell_integral(const R* q, const R* uA, const R* uB,
   return acc * L * inv_chis;
 }
 
-// Method A (Eq. kappa2) for one cell: int g (c delta) + (dg/dchi) (n . grad Phi)
-// over [chi_B, chi_A], both fields trilinear (qd, qg at the corners).  With
-// g = chi (chi_s - chi) / chi_s and dg/dchi = (chi_s - 2 chi) / chi_s the
-// integrand has degree <= 5: the same three-point rule is exact.
-template <typename R>
-__device__ __forceinline__ R cell_integral_a(const R* qd, const R* qg, const R* uA, const R* uB,
-                                             R L, R chiB, R DB, R inv_chis) {
-  R dd[4], dg[4];
-  dd[0] = qd[1] - qd[0]; dd[1] = qd[3] - qd[2]; dd[2] = qd[5] - qd[4]; dd[3] = qd[7] - qd[6];
-  dg[0] = qg[1] - qg[0]; dg[1] = qg[3] - qg[2]; dg[2] = qg[5] - qg[4]; dg[3] = qg[7] - qg[6];
-  const R du0 = uA[0] - uB[0], du1 = uA[1] - uB[1], du2 = uA[2] - uB[2];
-  const R cs[3] = {(R)GL3::c0, (R)GL3::c1, (R)GL3::c2};
-  const R ws[3] = {(R)GL3::w0, (R)GL3::w1, (R)GL3::w2};
-  R acc = 0;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const R c = cs[k];
-    const R u0 = fma(du0, c, uB[0]), u1 = fma(du1, c, uB[1]), u2 = fma(du2, c, uB[2]);
-    const R chik = fma(L, c, chiB);
-    const R rest = fma(-L, c, DB);               // chi_s - chi
-    const R vd = trilerp(qd, dd, u0, u1, u2);
-    const R vg = trilerp(qg, dg, u0, u1, u2);
-    acc = fma(ws[k], fma(chik * rest, vd, (rest - chik) * vg), acc);
-  }
-  return acc * L * inv_chis;
-}
-
 // The two integrals of the source-distance decomposition (Eq. Isources) over
 // one cell: ma = int chi Q dchi and mb = int chi^2 Q dchi on [chi_B, chi_A]
 // (degree <= 5 in chi: the three-point rule is exact).
@@ -206,26 +179,152 @@ __device__ __forceinline__ void cell_moments(const R* q, const R* uA, const R* u
   mb = b * L;
 }
 
-// int_{chi_B}^{chi_A} Q dchi of the trilinear field (a constant kernel, the
-// ISW integrand): cubic in chi, so the three-point rule is exact.
+// t where the lane's bit of m is set, else f.  The mask is read from a pair of
+// scalar registers: a row of selects on VCC in the short encoding takes the
+// SIMD 23 clocks each, this form 4.  (The masks are formed well ahead of their
+// use, so no wait states are due between the compare and the first select.)
+__device__ __forceinline__ float pick(unsigned long long m, float t, float f) {
+  float v;
+  asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(v) : "v"(f), "v"(t), "s"(m));
+  return v;
+}
+__device__ __forceinline__ double pick(unsigned long long m, double t, double f) {
+  const uint64_t tb = (uint64_t)__double_as_longlong(t), fb = (uint64_t)__double_as_longlong(f);
+  const float lo = pick(m, __uint_as_float((uint32_t)tb), __uint_as_float((uint32_t)fb));
+  const float hi = pick(m, __uint_as_float((uint32_t)(tb >> 32)), __uint_as_float((uint32_t)(fb >> 32)));
+  return __hiloint2double(__float_as_int(hi), __float_as_int(lo));
+}
+
+// Corner values q[i + 2 j] of one face and its bilinear coefficients
+// q0 + cx x + cy y + cxy x y.
 template <typename R>
-__device__ __forceinline__ R cell_integral_scalar(const R* q, const R* uA, const R* uB, R L) {
-  R dq[4];
-  dq[0] = q[1] - q[0];
-  dq[1] = q[3] - q[2];
-  dq[2] = q[5] - q[4];
-  dq[3] = q[7] - q[6];
-  const R du0 = uA[0] - uB[0], du1 = uA[1] - uB[1], du2 = uA[2] - uB[2];
-  const R cs[3] = {(R)GL3::c0, (R)GL3::c1, (R)GL3::c2};
-  const R ws[3] = {(R)GL3::w0, (R)GL3::w1, (R)GL3::w2};
-  R acc = 0;
+struct Face {
+  R q[4], cx, cy, cxy;
+  Face() = default;
+  __device__ __forceinline__ explicit Face(const R* v) {
 #pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const R c = cs[k];
-    acc = fma(ws[k], trilerp(q, dq, fma(du0, c, uB[0]), fma(du1, c, uB[1]), fma(du2, c, uB[2])),
-              acc);
+    for (int c = 0; c < 4; ++c) q[c] = v[c];
+    cx = q[1] - q[0];
+    cy = q[2] - q[0];
+    cxy = (q[3] - q[2]) - cx;
   }
-  return acc * L;
+  __device__ __forceinline__ R at(R x, R y) const {
+    return fma(y, fma(x, cxy, cy), fma(x, cx, q[0]));
+  }
+};
+
+template <typename R>
+__device__ __forceinline__ void swap_faces(Face<R>& a, Face<R>& b) {
+  const Face<R> t = a;
+  a = b;
+  b = t;
+}
+
+// The trilinear field along a piece from (xA, yA, zA) to (xB, yB, zB), with E
+// and X the faces z = 0 and z = 1 of the cell.  On either face the bilinear
+// value along the piece is, in t = (chi_A - chi) / L,
+//   E(t) = E0 (1 - t) + E1 t - cE t (1 - t),  cE = cxy (xB - xA) (yB - yA),
+// and 1 - z and z are linear in t, so
+//   Q(t) = u0 (1 - t)^2 + m t (1 - t) + u1 t^2 - t (1 - t) (cA (1 - t) + cB t)
+// with u0 and u1 the values at the two ends.  Against a quadratic kernel
+// g = gA (1 - t) + gB t + K t (1 - t) its integral is a sum of five products
+// (integrate_form): Eq. (Iclensing) exactly up to rounding, in about half the
+// operations of a three-point Gauss rule, most of all between two faces of one
+// axis (zA = 0, zB = 1), where u0 is the value the last cell ended with.  The
+// three builders round every piece they share alike.
+template <typename R>
+struct PieceForm {
+  R u0, m, u1, cA, cB;
+};
+
+// Value at the start of a piece (z = 0: exactly the entry face's).
+template <typename R>
+__device__ __forceinline__ R form_start(const Face<R>& e, const Face<R>& x, const R* fA) {
+  return fma(fA[2], x.at(fA[0], fA[1]), ((R)1 - fA[2]) * e.at(fA[0], fA[1]));
+}
+
+template <typename R>
+__device__ __forceinline__ PieceForm<R> form_general(const Face<R>& e, const Face<R>& x,
+                                                     const R* fA, const R* fB) {
+  const R eA = e.at(fA[0], fA[1]), eB = e.at(fB[0], fB[1]);
+  const R xA = x.at(fA[0], fA[1]), xB = x.at(fB[0], fB[1]);
+  const R dd = (fB[0] - fA[0]) * (fB[1] - fA[1]);
+  const R cE = e.cxy * dd, cX = x.cxy * dd;
+  const R zA = fA[2], zB = fB[2], wA = (R)1 - zA, wB = (R)1 - zB;
+  PieceForm<R> f;
+  f.u0 = fma(zA, xA, wA * eA);
+  f.u1 = fma(zB, xB, wB * eB);
+  f.m = fma(wA, eB, wB * eA) + fma(zA, xB, zB * xA);
+  f.cA = fma(zA, cX, wA * cE);
+  f.cB = fma(zB, cX, wB * cE);
+  return f;
+}
+
+// A piece that ends on the exit face (zB = 1); u0 from form_start.
+template <typename R>
+__device__ __forceinline__ PieceForm<R> form_out(const Face<R>& e, const Face<R>& x, R u0, R xa,
+                                                 R ya, R zA, R xb, R yb) {
+  const R eB = e.at(xb, yb), xA = x.at(xa, ya), xB = x.at(xb, yb);
+  const R dd = (xb - xa) * (yb - ya);
+  const R cE = e.cxy * dd, cX = x.cxy * dd;
+  const R wA = (R)1 - zA;
+  PieceForm<R> f;
+  f.u0 = u0;
+  f.u1 = xB;
+  const R we = wA * eB;   // rounded by itself, as in form_general with zB = 1
+  f.m = we + fma(zA, xB, xA);
+  f.cA = fma(zA, cX, wA * cE);
+  f.cB = cX;
+  return f;
+}
+
+// A piece from the entry face to the exit face (zA = 0, zB = 1).
+template <typename R>
+__device__ __forceinline__ PieceForm<R> form_through(const Face<R>& e, const Face<R>& x, R u0,
+                                                     R xa, R ya, R xb, R yb) {
+  const R dd = (xb - xa) * (yb - ya);
+  PieceForm<R> f;
+  f.u0 = u0;
+  f.u1 = x.at(xb, yb);
+  f.m = e.at(xb, yb) + x.at(xa, ya);
+  f.cA = e.cxy * dd;
+  f.cB = x.cxy * dd;
+  return f;
+}
+
+// 12 int_0^1 g Q dt of a piece against the kernel gA (1 - t) + gB t + K t (1 - t).
+template <typename R>
+__device__ __forceinline__ R integrate_form(const PieceForm<R>& f, R gA, R gB, R K) {
+  const R s = gA + gB;
+  const R a = fma((R)0.6, K, s), b = fma((R)0.2, K, (R)0.4 * s);
+  const R k20 = fma((R)2, gA, a), k02 = fma((R)2, gB, a), k11 = fma((R)0.4, K, s);
+  const R h21 = fma((R)0.2, gA, b), h12 = fma((R)0.2, gB, b);
+  return fma(f.u0, k20, fma(f.m, k11, fma(f.u1, k02, -fma(f.cA, h21, f.cB * h12))));
+}
+
+// 12 int_0^1 Q dt.
+template <typename R>
+__device__ __forceinline__ R integrate_constant(const PieceForm<R>& f) {
+  return fma((R)4, f.u0 + f.u1, fma((R)2, f.m, -(f.cA + f.cB)));
+}
+
+// One face crossed, along axis 0 in the lanes of m0, axis 1 in those of m1 and
+// axis 2 in the others: the four values of that face move to the entry side,
+// the four of the new exit face F_j (j = i_a + 2 i_b over the two other axes
+// a < b) come in.
+template <typename R>
+__device__ __forceinline__ void shift_face(R* E, R* X, unsigned long long m0,
+                                           unsigned long long m1, const R* F) {
+  const unsigned long long m01 = m0 | m1;
+  const R e0 = pick(m0, E[1], pick(m1, E[2], X[0]));
+  const R e1 = pick(m0, F[0], pick(m1, E[3], X[1]));
+  const R e2 = pick(m0, E[3], pick(m1, F[0], X[2]));
+  const R e3 = pick(m01, F[1], X[3]);
+  const R x0 = pick(m0, X[1], pick(m1, X[2], F[0]));
+  const R x1 = pick(m0, F[2], pick(m1, X[3], F[1]));
+  const R x2 = pick(m0, X[3], F[2]);
+  E[0] = e0; E[1] = e1; E[2] = e2; E[3] = e3;
+  X[0] = x0; X[1] = x1; X[2] = x2; X[3] = F[3];
 }
 
 // FNV-1a, 64 bit, over the 8 little-endian bytes of w.
@@ -290,6 +389,13 @@ __device__ __forceinline__ void zorder_tile(int64_t k, int W, int H, int& x, int
   }
   x = x0;
   y = y0;
+}
+
+// Position of a lane's ray in its 8 x 8 tile, Z order: each quad of lanes is a
+// 2 x 2 block of the map.
+__device__ __forceinline__ void zorder_lane(int lane, int& x, int& y) {
+  x = (lane & 1) | ((lane >> 1) & 2) | ((lane >> 2) & 4);
+  y = ((lane >> 1) & 1) | ((lane >> 2) & 2) | ((lane >> 3) & 4);
 }
 
 // Persistent launches: one work counter per chiplet (XCD).  Workgroups are
