@@ -20,10 +20,10 @@
 // plane once and keeps the per-plane partial stencils of the last four planes
 // in registers, so each vertex costs 16 LDS reads and ~80 arithmetic
 // operations.  Whole-grid builds take 64 x 16 x 16 columns (1024 threads;
-// staging with the halo reads 1.5 potential values per vertex) and write the
-// records with non-temporal stores (the 3 GiB tensor of a 512^3 grid does not
-// fit any cache); small boxes take 64 x 4 x 32 columns and ordinary stores,
-// since the march reads them right away.
+// staging with the halo reads 1.5 potential values per vertex) or 64 x 8 x 32
+// ones and write the records with non-temporal stores (the 3 GiB tensor of a 512^3 grid does not
+// fit any cache); small grids and boxes take columns of 64 x 4 with 256
+// threads (launch_vt) and ordinary stores, since the march reads them right away.
 #include "rr_internal.hpp"
 
 namespace rr {
@@ -79,12 +79,13 @@ __global__ __launch_bounds__(64 * TY) void vertex_tensor_uniform_kernel(const In
   constexpr int NT = TX * TY;                 // threads
   constexpr int PX = TX + 3, PY = TY + 3;     // staged plane: halo 2 below, 1 above
   __shared__ Acc plane[2][PY * PX];
-  // FP64 records of whole-grid builds leave through LDS: each wavefront (one
-  // row of 64 vertices) writes its 3 KiB row with contiguous 16-byte stores
-  // instead of three 16-byte stores per lane at a 48-byte stride (2.2 ->
-  // 1.8 ms for 512^3).  FP32 rows keep per-lane stores: the staging buffer
-  // would cost the second workgroup per CU (0.78 -> 0.99 ms).
-  constexpr bool kRowStore = kNT && sizeof(Acc) == 8;
+  // Records of whole-grid builds leave through LDS: each wavefront (one row of
+  // 64 vertices) writes its row with contiguous stores instead of three per
+  // lane at the stride of a record.  512^3 FP64: 2.2 -> 1.8 ms, and 1.38 with
+  // the next plane read ahead; FP32 in 64 x 8 columns: 400^3 517 -> 337 us,
+  // 256^3 112 -> 99, 501^3 931 -> 893.  FP32 in 64 x 16 columns (512^3 and up)
+  // keeps per-lane stores: there staging costs the second workgroup per CU.
+  constexpr bool kRowStore = kNT && !(sizeof(Acc) == 4 && TY == 16);
   __shared__ __align__(16) Acc rowbuf[kRowStore ? TY : 1][kRowStore ? TX * RW : 1];
 
   const int b = blockIdx.x;
@@ -99,10 +100,11 @@ __global__ __launch_bounds__(64 * TY) void vertex_tensor_uniform_kernel(const In
   i = i >= n ? i - n : i;
   j = j >= n ? j - n : j;
   const int64_t nn = (int64_t)n * n;
-  // the wavefront's row is whole, does not wrap and starts 16-byte aligned
+  // the wavefront's row of n_row vertices does not wrap
   int i_row = V.ox + li0;
   i_row = i_row >= n ? i_row - n : i_row;
-  const bool row_ok = kRowStore && li0 + TX <= V.sx && lj0 + ty < V.sy && i_row + TX <= n;
+  const int n_row = min(TX, V.sx - li0);
+  const bool row_ok = kRowStore && i_row + n_row <= n;
 
   // per-plane partial stencils, history over planes (index 0 = oldest)
   Acc XX[2], YY[2], XY[2];     // planes k-1, k
@@ -194,7 +196,7 @@ __global__ __launch_bounds__(64 * TY) void vertex_tensor_uniform_kernel(const In
     DX[3][0] = dx[1]; DX[3][1] = dx[2];
     DY[3][0] = dy1; DY[3][1] = dy2;
 
-    if (p >= k0 + 1 && mine) {
+    if (p >= k0 + 1 && lj0 + ty < V.sy) {
       // vertex k = p - 1: Z/DX/DY[0..3] are planes k-2..k+1; XX/YY/XY[0..1] are k-1, k
       const int k = p - 1 >= n ? p - 1 - n : p - 1;
       Acc rec[6];
@@ -220,22 +222,24 @@ __global__ __launch_bounds__(64 * TY) void vertex_tensor_uniform_kernel(const In
       }
       if (row_ok) {
         // lanes write their records side by side in LDS, then read back
-        // 16-byte chunks of the row in order (LDS operations of one
-        // wavefront complete in order; the empty asm statements keep the
-        // compiler from moving the accesses across each other)
+        // chunks of the row in order: 16 bytes in FP64, 8 in FP32, whose rows
+        // start at any multiple of 8 (LDS operations of one wavefront complete
+        // in order; the empty asm statements keep the compiler from moving the
+        // accesses across each other)
         Acc* rb = rowbuf[kRowStore ? ty : 0];
+        typedef Acc chunk_t __attribute__((ext_vector_type(2)));
+        constexpr int kChunks = RW / 2;      // per record
+        chunk_t* rc = reinterpret_cast<chunk_t*>(rb);
 #pragma unroll
-        for (int c = 0; c < RW; ++c) rb[tx * RW + c] = rec[c];
+        for (int c = 0; c < kChunks; ++c) rc[tx * kChunks + c] = chunk_t{rec[2 * c], rec[2 * c + 1]};
         __asm__ volatile("" ::: "memory");
-        typedef Acc chunk_t __attribute__((ext_vector_type(16 / sizeof(Acc))));
-        constexpr int kE = 16 / sizeof(Acc), kChunks = TX * RW / kE;
-        Acc* dst = tv + ((int64_t)k * nn + (int64_t)j * n + i_row) * RW;
+        chunk_t* dst =
+            reinterpret_cast<chunk_t*>(tv + ((int64_t)k * nn + (int64_t)j * n + i_row) * RW);
 #pragma unroll
-        for (int m = tx; m < kChunks; m += TX)
-          __builtin_nontemporal_store(*reinterpret_cast<const chunk_t*>(rb + m * kE),
-                                      reinterpret_cast<chunk_t*>(dst + m * kE));
+        for (int m = tx; m < TX * kChunks; m += TX)
+          if (m < n_row * kChunks) __builtin_nontemporal_store(rc[m], dst + m);
         __asm__ volatile("" ::: "memory");
-      } else {
+      } else if (mine) {
         store_vertex<kNT>(tv + ((int64_t)k * nn + (int64_t)j * n + i) * RW, rec);
       }
     }
@@ -245,43 +249,113 @@ __global__ __launch_bounds__(64 * TY) void vertex_tensor_uniform_kernel(const In
   }
 }
 
-// Cell-centre tensor (Eq. tidalexample, cell size 1), one cell per thread,
-// for the nearest-grid-point integral (Eq. Iclensing_ngp).  Second
-// differences as differences of differences, mixed ones over the four
-// diagonal neighbours; open grids leave the outer cell layer NaN (no stencil).
-template <typename In, typename Acc>
+// Cell-centre tensor (Eq. tidalexample, cell size 1) for the nearest-grid-point
+// integral (Eq. Iclensing_ngp).  Second differences as differences of
+// differences, mixed ones over the four diagonal neighbours; open grids leave
+// the outer cell layer NaN (no stencil).
+//
+// Memory bound (4 bytes in, 24 out in FP32).  A wavefront owns a row of 64
+// cells and marches kz cells along z, reading nine values of each plane and
+// keeping three planes in registers; its records leave through LDS as
+// contiguous stores.  One cell per thread, 19 gathered values each and three
+// stores at the stride of a record took 171 us for 256^3 FP32 (2.8 TB/s of
+// algorithmic traffic); this takes 94 us (5.0 TB/s);
+// 512^3 1345 -> 926, FP64 256^3 368 -> 169.
+template <typename In, typename Acc, bool kNT>
 __global__ __launch_bounds__(256) void centre_tensor_uniform_kernel(const In* __restrict__ phi,
                                                                     Acc* __restrict__ tc, int n,
-                                                                    int open) {
+                                                                    int open, int kz) {
+  typedef Acc chunk_t __attribute__((ext_vector_type(2)));
+  __shared__ __align__(16) chunk_t rows[4][TX * 3];
+  const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
+  const int i0 = blockIdx.x * TX, j = blockIdx.y * 4 + ty, k0 = blockIdx.z * kz;
+  if (j >= n) return;   // whole wavefronts
   const int64_t nn = (int64_t)n * n;
-  const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (c >= nn * n) return;
-  const int i = (int)(c % n), j = (int)((c / n) % n), k = (int)(c / nn);
-  Acc rec[6];
-  if (open && (i < 1 || j < 1 || k < 1 || i > n - 2 || j > n - 2 || k > n - 2)) {
+  const int n_row = min(TX, n - i0), i = min(i0 + tx, n - 1);
+  const int xs[3] = {i == 0 ? n - 1 : i - 1, i, i + 1 == n ? 0 : i + 1};
+  const int ys[3] = {(j == 0 ? n - 1 : j - 1) * n, j * n, (j + 1 == n ? 0 : j + 1) * n};
+  In v[3][3];
+  auto fetch = [&](int k) {
+    const In* src = phi + (int64_t)(k < 0 ? k + n : (k >= n ? k - n : k)) * nn;
 #pragma unroll
-    for (int u = 0; u < 6; ++u) rec[u] = (Acc)__builtin_nan("");
-  } else {
-    const int im = i == 0 ? n - 1 : i - 1, ip = i + 1 == n ? 0 : i + 1;
-    const int jm = j == 0 ? n - 1 : j - 1, jp = j + 1 == n ? 0 : j + 1;
-    const int km = k == 0 ? n - 1 : k - 1, kp = k + 1 == n ? 0 : k + 1;
-    auto P = [&](int x, int y, int z) -> Acc { return (Acc)phi[(int64_t)z * nn + (int64_t)y * n + x]; };
-    const Acc c0 = P(i, j, k);
-    rec[0] = (P(ip, j, k) - c0) - (c0 - P(im, j, k));
-    rec[1] = (P(i, jp, k) - c0) - (c0 - P(i, jm, k));
-    rec[2] = (P(i, j, kp) - c0) - (c0 - P(i, j, km));
-    rec[3] = ((P(ip, jp, k) - P(ip, jm, k)) - (P(im, jp, k) - P(im, jm, k))) * (Acc)0.25;
-    rec[4] = ((P(ip, j, kp) - P(ip, j, km)) - (P(im, j, kp) - P(im, j, km))) * (Acc)0.25;
-    rec[5] = ((P(i, jp, kp) - P(i, jp, km)) - (P(i, jm, kp) - P(i, jm, km))) * (Acc)0.25;
+    for (int b = 0; b < 3; ++b)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) v[b][a] = src[ys[b] + xs[a]];
+  };
+  // planes k - 1, k, k + 1: the cell's cross (c, x-, x+, y-, y+); plane k also
+  // the second differences and the mixed one in x and y
+  Acc lo[5], mid[5], hi[5], txx = 0, tyy = 0, txy = 0;
+  const int k_end = min(k0 + kz, n);
+  auto take = [&](Acc* p) {
+    p[0] = (Acc)v[1][1];
+    p[1] = (Acc)v[1][0];
+    p[2] = (Acc)v[1][2];
+    p[3] = (Acc)v[0][1];
+    p[4] = (Acc)v[2][1];
+  };
+  auto in_plane = [&](const Acc* p) {
+    txx = (p[2] - p[0]) - (p[0] - p[1]);
+    tyy = (p[4] - p[0]) - (p[0] - p[3]);
+    txy = (((Acc)v[2][2] - (Acc)v[0][2]) - ((Acc)v[2][0] - (Acc)v[0][0])) * (Acc)0.25;
+  };
+  fetch(k0 - 1);
+  take(lo);
+  fetch(k0);
+  take(mid);
+  in_plane(mid);
+  fetch(k0 + 1);
+  for (int k = k0; k < k_end; ++k) {
+    take(hi);
+    Acc rec[6];
+    rec[0] = txx;
+    rec[1] = tyy;
+    rec[2] = (hi[0] - mid[0]) - (mid[0] - lo[0]);
+    rec[3] = txy;
+    rec[4] = ((hi[2] - lo[2]) - (hi[1] - lo[1])) * (Acc)0.25;
+    rec[5] = ((hi[4] - lo[4]) - (hi[3] - lo[3])) * (Acc)0.25;
+    if (open && (i < 1 || j < 1 || k < 1 || i > n - 2 || j > n - 2 || k > n - 2)) {
+#pragma unroll
+      for (int u = 0; u < 6; ++u) rec[u] = (Acc)__builtin_nan("");
+    }
+    in_plane(hi);
+    if (k + 1 < k_end) fetch(k + 2);   // in flight while the row is stored
+#pragma unroll
+    for (int u = 0; u < 5; ++u) {
+      lo[u] = mid[u];
+      mid[u] = hi[u];
+    }
+    // LDS operations of one wavefront complete in order; the empty statements
+    // keep the compiler from moving the accesses across each other
+    chunk_t* rc = rows[ty];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) rc[tx * 3 + u] = chunk_t{rec[2 * u], rec[2 * u + 1]};
+    __asm__ volatile("" ::: "memory");
+    chunk_t* dst = reinterpret_cast<chunk_t*>(tc + ((int64_t)k * nn + (int64_t)j * n + i0) * 6);
+#pragma unroll
+    for (int m = tx; m < TX * 3; m += TX)
+      if (m < n_row * 3) {
+        if constexpr (kNT) __builtin_nontemporal_store(rc[m], dst + m);
+        else dst[m] = rc[m];
+      }
+    __asm__ volatile("" ::: "memory");
   }
-  store_vertex<false>(tc + c * 6, rec);
 }
 
 template <typename In, typename Acc>
 hipError_t launch_ct(int n, int open, const void* phi, void* tc, hipStream_t s) {
-  const int64_t blocks = ((int64_t)n * n * n + 255) / 256;
-  hipLaunchKernelGGL((centre_tensor_uniform_kernel<In, Acc>), dim3((unsigned)blocks), dim3(256),
-                     0, s, (const In*)phi, (Acc*)tc, n, open);
+  // cells along z per workgroup: 16, fewer where that leaves the chip short of
+  // four workgroups per compute unit
+  const int ntx = (n + TX - 1) / TX, nty = (n + 3) / 4;
+  int kz = 16;
+  while (kz > 2 && (int64_t)ntx * nty * ((n + kz - 1) / kz) < 1024) kz /= 2;
+  const dim3 grid(ntx, nty, (n + kz - 1) / kz);
+  // records beyond the last-level cache are stored past it
+  if ((int64_t)n * n * n * 6 * (int64_t)sizeof(Acc) > (256ll << 20))
+    hipLaunchKernelGGL((centre_tensor_uniform_kernel<In, Acc, true>), grid, dim3(256), 0, s,
+                       (const In*)phi, (Acc*)tc, n, open, kz);
+  else
+    hipLaunchKernelGGL((centre_tensor_uniform_kernel<In, Acc, false>), grid, dim3(256), 0, s,
+                       (const In*)phi, (Acc*)tc, n, open, kz);
   return hipGetLastError();
 }
 
@@ -311,11 +385,27 @@ hipError_t launch_vt(int n, int open, const int* lo, const int* size, const void
   }
   V.ox = o[0]; V.oy = o[1]; V.oz = o[2];
   V.sx = size[0]; V.sy = size[1]; V.sz = size[2];
-  const int64_t nv = (int64_t)V.sx * V.sy * V.sz;
+  // Boxes that give the chip fewer than two workgroups per compute unit in the
+  // shapes below take columns of 64 x 4, as deep as leaves it that many: 64^3
+  // FP64 29 -> 10 us, the vertex box of a 512^3 cone's segment 22 -> 8 us.
+  auto columns = [&](int ty, int kz) {
+    return (int64_t)((V.sx + TX - 1) / TX) * ((V.sy + ty - 1) / ty) * ((V.sz + kz - 1) / kz);
+  };
+  constexpr int64_t kFill = 512;
   // boxes beyond 1/8 of the grid stream through HBM like the whole grid
-  if (8 * nv > (int64_t)n * n * n)
-    return launch_shape<In, Acc, 16, 16, true>(V, n, open, phi, tv, s);
-  return launch_shape<In, Acc, 4, 32, false>(V, n, open, phi, tv, s);
+  if (8 * (int64_t)V.sx * V.sy * V.sz > (int64_t)n * n * n) {
+    // FP64, and FP32 from 512 a side (where both shapes stream at the memory's
+    // rate: 512^3 0.84 ms against 0.86, 640^3 1.69 against 1.70): 64 x 16 x 16,
+    // the least halo.  Smaller FP32 grids: 64 x 8 x 32 with rows stored through
+    // LDS (figures above).
+    if ((sizeof(Acc) == 8 || n >= 512) && columns(16, 16) >= kFill)
+      return launch_shape<In, Acc, 16, 16, true>(V, n, open, phi, tv, s);
+    if constexpr (sizeof(Acc) == 4)
+      if (columns(8, 32) >= kFill) return launch_shape<In, Acc, 8, 32, true>(V, n, open, phi, tv, s);
+  }
+  if (columns(4, 32) >= kFill) return launch_shape<In, Acc, 4, 32, false>(V, n, open, phi, tv, s);
+  if (columns(4, 8) >= kFill) return launch_shape<In, Acc, 4, 8, false>(V, n, open, phi, tv, s);
+  return launch_shape<In, Acc, 4, 4, false>(V, n, open, phi, tv, s);
 }
 
 }  // namespace
