@@ -577,9 +577,9 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
       gA = gB;
       hA = hB;
       chiA = chiB;
-      fA[0] = pick(m0, (R)0, fB[0]);
-      fA[1] = pick(m1, (R)0, fB[1]);
-      fA[2] = pick(m0 | m1, fB[2], (R)0);
+      fA[0] = pick(settle(m0), (R)0, fB[0]);
+      fA[1] = pick(settle(m1), (R)0, fB[1]);
+      fA[2] = pick(settle(m0 | m1), fB[2], (R)0);
       if constexpr (kMode != kNgp) {
         rec.hold(sum);
         R F[4], F2[4];
@@ -801,29 +801,53 @@ __global__ __launch_bounds__(256) void fill_kernel(double* __restrict__ p, int64
 // the observer: the moment state holds what lies below the nearest source,
 // and summing the pieces from the observer outwards gives int chi Q and
 // int chi^2 Q below each source in turn, kappa_j = A_j - B_j / chi_s,j.
-// FP64 throughout; one thread per ray.
+// FP64 throughout; one thread per ray, eight sources at a time staged through
+// LDS so that pieces and kappa (ray-major) move as 128- and 64-byte runs: 245 ->
+// 79 us for 1024^2 rays and ten sources, whose 252 MB take 53 us at the
+// memory's copy rate.
+constexpr int kPieceTile = 8;
 template <typename R>
 __global__ __launch_bounds__(256) void kappa_from_pieces_kernel(const R* __restrict__ mom,
                                                                 const double* __restrict__ pieces,
                                                                 const double* __restrict__ src,
                                                                 int ns, int64_t nr,
                                                                 double* __restrict__ kappa) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nr) return;
-  double A, B;
-  if constexpr (sizeof(R) == 4) {
-    const float4 m = reinterpret_cast<const float4*>(mom)[r];
-    A = (double)m.x - (double)m.y;
-    B = (double)m.z - (double)m.w;
-  } else {
-    const double2 m = reinterpret_cast<const double2*>(mom)[r];
-    A = m.x;
-    B = m.y;
+  __shared__ double2 pc[256][kPieceTile + 1];
+  const int64_t r0 = (int64_t)blockIdx.x * 256;
+  const int rays = (int)(nr - r0 < 256 ? nr - r0 : 256);
+  const int t = threadIdx.x;
+  double A = 0.0, B = 0.0;
+  if (t < rays) {
+    if constexpr (sizeof(R) == 4) {
+      const float4 m = reinterpret_cast<const float4*>(mom)[r0 + t];
+      A = (double)m.x - (double)m.y;
+      B = (double)m.z - (double)m.w;
+    } else {
+      const double2 m = reinterpret_cast<const double2*>(mom)[r0 + t];
+      A = m.x;
+      B = m.y;
+    }
   }
-  for (int j = ns - 1; j >= 0; --j) {
-    kappa[r * ns + j] = A - B / src[j];
-    A += pieces[(r * ns + j) * 2 + 0];
-    B += pieces[(r * ns + j) * 2 + 1];
+  for (int j1 = ns; j1 > 0; j1 -= kPieceTile) {
+    const int j0 = j1 > kPieceTile ? j1 - kPieceTile : 0;   // sources j0 .. j1 - 1
+    __syncthreads();
+    for (int e = t; e < 256 * kPieceTile; e += 256) {
+      const int r = e / kPieceTile, j = j0 + e % kPieceTile;
+      if (r < rays && j < j1)
+        pc[r][e % kPieceTile] = reinterpret_cast<const double2*>(pieces)[(r0 + r) * ns + j];
+    }
+    __syncthreads();
+    for (int j = j1 - 1; j >= j0; --j) {
+      const double2 p = pc[t][j - j0];
+      pc[t][j - j0].x = A - B / src[j];
+      A += p.x;
+      B += p.y;
+    }
+    __syncthreads();
+    for (int e = t; e < 256 * kPieceTile; e += 256) {
+      const int r = e / kPieceTile, j = j0 + e % kPieceTile;
+      if (r < rays && j < j1) kappa[(r0 + r) * ns + j] = pc[r][e % kPieceTile].x;
+    }
   }
 }
 

@@ -181,8 +181,13 @@ __device__ __forceinline__ void cell_moments(const R* q, const R* uA, const R* u
 
 // t where the lane's bit of m is set, else f.  The mask is read from a pair of
 // scalar registers: a row of selects on VCC in the short encoding takes the
-// SIMD 23 clocks each, this form 4.  (The masks are formed well ahead of their
-// use, so no wait states are due between the compare and the first select.)
+// SIMD 23 clocks each, this form 4.  A mask goes through settle() first: two
+// wait states are due between the compare that writes it and a select that
+// reads it, and the compiler does not count them for these statements.
+__device__ __forceinline__ unsigned long long settle(unsigned long long m) {
+  asm volatile("s_nop 1" : "+s"(m));
+  return m;
+}
 __device__ __forceinline__ float pick(unsigned long long m, float t, float f) {
   float v;
   asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(v) : "v"(f), "v"(t), "s"(m));
@@ -315,6 +320,8 @@ __device__ __forceinline__ R integrate_constant(const PieceForm<R>& f) {
 template <typename R>
 __device__ __forceinline__ void shift_face(R* E, R* X, unsigned long long m0,
                                            unsigned long long m1, const R* F) {
+  m0 = settle(m0);
+  m1 = settle(m1);
   const unsigned long long m01 = m0 | m1;
   const R e0 = pick(m0, E[1], pick(m1, E[2], X[0]));
   const R e1 = pick(m0, F[0], pick(m1, E[3], X[1]));
