@@ -419,7 +419,7 @@ rr_status rr_trace_rays_adjoint(rr_plan p, rr_tensor t, const rr_field_desc* f,
  *  - n_bundles <= 1024, else RR_ERR_CAPACITY (nothing enqueued).
  *  - tp->persistent: 1 = persistent workgroups (16 wavefronts per compute
  *    unit) fed by the queue counter; 0 or -1 = one wavefront per 8x8 tile
- *    (256-thread workgroups).  The march is never split into passes.
+ *    (64- or 256-thread workgroups by the number of tiles).  The march is never split into passes.
  *  - No hipMalloc, hipFree or other allocating call; host memory is the
  *    stack only.
  *  - Every call on one GPU shares that GPU's array, which keeps the last

@@ -510,19 +510,20 @@ __global__ __launch_bounds__(kTX * kTY) void transpose_kernel(const float* __res
 }  // namespace
 
 hipError_t launch_adjoint_uniform(const TraceArgs& a, const float* dl_dkappa, float* lam,
-                                  float* dl_dphi, hipStream_t s) {
+                                  float* dl_dphi, int block, hipStream_t s) {
   const int64_t nv = (int64_t)a.n * a.n * a.n;
   hipLaunchKernelGGL(fill_zero_kernel, dim3(2048), dim3(256), 0, s, lam, nv * 6);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (a.n_tiles > 0) {
-    int64_t blocks = (a.n_tiles + 3) / 4;
+    const int wpb = block / 64;
+    int64_t blocks = (a.n_tiles + wpb - 1) / wpb;
     blocks = (blocks + 7) / 8 * 8;
     if (nv < (int64_t)0xffffffffll)
-      hipLaunchKernelGGL(scatter_kernel<uint32_t>, dim3((unsigned)blocks), dim3(256), 0, s, a,
+      hipLaunchKernelGGL(scatter_kernel<uint32_t>, dim3((unsigned)blocks), dim3(block), 0, s, a,
                          dl_dkappa, lam);
     else
-      hipLaunchKernelGGL(scatter_kernel<uint64_t>, dim3((unsigned)blocks), dim3(256), 0, s, a,
+      hipLaunchKernelGGL(scatter_kernel<uint64_t>, dim3((unsigned)blocks), dim3(block), 0, s, a,
                          dl_dkappa, lam);
     e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -863,16 +863,17 @@ void march_octree_persistent(Tree T, const R* __restrict__ cv, TraceArgs a) {
 
 template <typename R, bool kDebug, int kMode, typename Off>
 hipError_t launch_march(const Tree& T, const void* cv, const TraceArgs& a, int persistent,
-                        int grid_waves, hipStream_t s) {
+                        int block, int grid_waves, hipStream_t s) {
   if (persistent) {
     const int blocks = (grid_waves + 3) / 4;
     hipLaunchKernelGGL((march_octree_persistent<R, kDebug, kMode, Off>), dim3(blocks), dim3(256), 0, s, T,
                        (const R*)cv, a);
   } else {
-    int64_t blocks = (a.n_tiles + 3) / 4;
+    const int wpb = block / 64;
+    int64_t blocks = (a.n_tiles + wpb - 1) / wpb;
     if (blocks == 0) return hipSuccess;
     blocks = (blocks + 7) / 8 * 8;
-    hipLaunchKernelGGL((march_octree_kernel<R, kDebug, kMode, Off>), dim3((unsigned)blocks), dim3(256), 0, s,
+    hipLaunchKernelGGL((march_octree_kernel<R, kDebug, kMode, Off>), dim3((unsigned)blocks), dim3(block), 0, s,
                        T, (const R*)cv, a);
   }
   return hipGetLastError();
@@ -931,36 +932,36 @@ namespace {
 
 template <typename R, int kMode>
 hipError_t launch_march_w(const Tree& T, const void* cv, int64_t n_cells, const TraceArgs& a,
-                          int persistent, int grid_waves, hipStream_t s) {
+                          int persistent, int block, int grid_waves, hipStream_t s) {
   const bool dbg = a.hash || a.log || a.count;
   // 32-bit cell indices and byte offsets when the corner blocks are below 4 GiB
   const bool small = n_cells * 48 * (int64_t)sizeof(R) < (1ll << 32);
   if (small)
-    return dbg ? launch_march<R, true, kMode, uint32_t>(T, cv, a, persistent, grid_waves, s)
-               : launch_march<R, false, kMode, uint32_t>(T, cv, a, persistent, grid_waves, s);
-  return dbg ? launch_march<R, true, kMode, uint64_t>(T, cv, a, persistent, grid_waves, s)
-             : launch_march<R, false, kMode, uint64_t>(T, cv, a, persistent, grid_waves, s);
+    return dbg ? launch_march<R, true, kMode, uint32_t>(T, cv, a, persistent, block, grid_waves, s)
+               : launch_march<R, false, kMode, uint32_t>(T, cv, a, persistent, block, grid_waves, s);
+  return dbg ? launch_march<R, true, kMode, uint64_t>(T, cv, a, persistent, block, grid_waves, s)
+             : launch_march<R, false, kMode, uint64_t>(T, cv, a, persistent, block, grid_waves, s);
 }
 
 }  // namespace
 
-hipError_t OctreeTensor::march(const TraceArgs& a, int persistent, int grid_waves,
+hipError_t OctreeTensor::march(const TraceArgs& a, int persistent, int block, int grid_waves,
                                hipStream_t s) {
   if (a.n_tiles == 0) return hipSuccess;
   Tree T{child_oct_dev, reinterpret_cast<const int4*>(oct_info), n, (int64_t)n * n * n};
   if (a.mode == kOctNgp) {   // cell-centre records, 6 per cell
     if (precision == RR_PREC_FP32_KAHAN)
-      return launch_march_w<float, kOctNgp>(T, centre, n_cells, a, persistent, grid_waves, s);
-    return launch_march_w<double, kOctNgp>(T, centre, n_cells, a, persistent, grid_waves, s);
+      return launch_march_w<float, kOctNgp>(T, centre, n_cells, a, persistent, block, grid_waves, s);
+    return launch_march_w<double, kOctNgp>(T, centre, n_cells, a, persistent, block, grid_waves, s);
   }
   if (a.mode == kOctSources) {
     if (precision == RR_PREC_FP32_KAHAN)
-      return launch_march_w<float, kOctSources>(T, corners, n_cells, a, persistent, grid_waves, s);
-    return launch_march_w<double, kOctSources>(T, corners, n_cells, a, persistent, grid_waves, s);
+      return launch_march_w<float, kOctSources>(T, corners, n_cells, a, persistent, block, grid_waves, s);
+    return launch_march_w<double, kOctSources>(T, corners, n_cells, a, persistent, block, grid_waves, s);
   }
   if (precision == RR_PREC_FP32_KAHAN)
-    return launch_march_w<float, kOctTidal>(T, corners, n_cells, a, persistent, grid_waves, s);
-  return launch_march_w<double, kOctTidal>(T, corners, n_cells, a, persistent, grid_waves, s);
+    return launch_march_w<float, kOctTidal>(T, corners, n_cells, a, persistent, block, grid_waves, s);
+  return launch_march_w<double, kOctTidal>(T, corners, n_cells, a, persistent, block, grid_waves, s);
 }
 
 }  // namespace rr

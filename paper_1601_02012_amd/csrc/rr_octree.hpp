@@ -29,11 +29,12 @@ struct OctreeTensor {
                               std::string* msg);
   hipError_t count_coarse_corners(hipStream_t s);   // once, at creation (tree only)
   hipError_t build(const void* values, int dtype, hipStream_t s);
-  hipError_t march(const TraceArgs& a, int persistent, int grid_waves, hipStream_t s);
+  // block: threads of a one-wavefront-per-tile launch (64 or 256)
+  hipError_t march(const TraceArgs& a, int persistent, int block, int grid_waves, hipStream_t s);
   ~OctreeTensor();
 };
 
 hipError_t launch_adjoint_uniform(const TraceArgs& a, const float* dl_dkappa, float* lam,
-                                  float* dl_dphi, hipStream_t s);
+                                  float* dl_dphi, int block, hipStream_t s);
 
 }  // namespace rr
