@@ -161,6 +161,12 @@ __device__ __forceinline__ uint64_t quad_first(uint64_t x) {
   return ((uint64_t)quad_first((uint32_t)(x >> 32)) << 32) | quad_first((uint32_t)x);
 }
 
+// The largest x of the quad.
+__device__ __forceinline__ int quad_max(int x) {
+  const int y = max(x, __builtin_amdgcn_update_dpp(0, x, 0xb1, 0xf, 0xf, false));
+  return max(y, __builtin_amdgcn_update_dpp(0, y, 0x4e, 0xf, 0xf, false));
+}
+
 // One ray, in the ray's own frame: along each axis, corner bit 0 is the
 // vertex layer of the face the ray enters through and bit 1 the layer of the
 // face it leaves through, and the local coordinate f runs from 0 (entry face)
@@ -436,10 +442,22 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
       // one record per lane: all 64 lanes march (matrix instructions ignore
       // the execution mask), and the four lanes of every quad are in one cell
       // and share its frame
-      bool run = __ballot(te[2] > lim) == all;
+      bool run = __ballot(te[2] > lim) == all, part = true;
       if constexpr (sizeof(R) == 4 && kMode != kNgp) {
-        const Off w = w01 + oX[2], w2 = oX[0] + oX[1];
-        run = run && (__ballot(quad_first(w) == w) & __ballot(quad_first(w2) == w2)) == ~0ull;
+        if (run) {
+          const Off w2 = oX[0] + oX[1];
+          run = (__ballot(quad_first(w01) == w01) & __ballot(quad_first(w2) == w2)) == ~0ull;
+          if (run) {
+            // lanes of one column of cells, but in different layers of axis 2 (a
+            // window that starts with a plane of axis 0 or 1 across a quad
+            // leaves its lanes one crossing apart): those behind cross a face
+            // alone, once, and the runs go on
+            const int adv = down2 ? -(int)pp[2] : (int)pp[2];
+            const bool behind = adv < quad_max(adv);
+            run = __ballot(behind) == 0ull;
+            part = run || behind;
+          }
+        }
       }
       if (run) {
         // ---- every lane leaves its cell through axis 2 alone
@@ -545,47 +563,49 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
       const unsigned long long ms =
           __ballot(side > te[2]) & __ballot(side > halt) & __ballot(te[0] != te[1]);
       if ((m2 | ms) != all) break;
-      const double chiB = fmax(te[2], side);
-      const unsigned long long m0 = ms & __ballot(te[0] > te[1]), m1 = ms & ~m0;
-      R fB[3];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) fB[k] = (R)1 - absd[k] * (R)(chiB - te[k]);
-      R ngp = 0;   // NGP: the value of the cell being left
-      if constexpr (kMode == kNgp) ngp = point_value<R, Off, kMode>(tv, cell_offset(), P);
-      const bool k2 = te[2] == chiB, k0 = te[0] == chiB, k1 = te[1] == chiB;
-      if (k2) next_layer(2);
-      if (k0) next_layer(0);
-      if (k1) next_layer(1);
-      // the four records of the new exit face, in flight during the integral
-      FaceRecords<R, Off, kMode> rec;
-      if constexpr (kMode != kNgp) {
-        const Off w0 = (k0 ? oX[0] : oE[0]) + (k1 ? oX[1] : oE[1]) + (k2 ? oX[2] : oE[2]);
-        rec.load(tv, w0, k0 ? oX[1] - oE[1] : oX[0] - oE[0], k2 ? oX[1] - oE[1] : oX[2] - oE[2]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      const R L = (R)(chiA - chiB);
-      R gB, hB;
-      kernel(chiB, gB, hB);
-      if constexpr (kMode == kNgp) {
-        add_ngp(ngp, chiB, L);
-      } else {
-        const PieceForm<R> q = form_general(Face<R>(E), Face<R>(X), fA, fB);
-        PieceForm<R> q2 = q;
-        if constexpr (kTwo) q2 = form_general(Face<R>(E2), Face<R>(X2), fA, fB);
-        add_piece(q, q2, L, gA, gB, hA, hB, (R)0);
-      }
-      gA = gB;
-      hA = hB;
-      chiA = chiB;
-      fA[0] = pick(settle(m0), (R)0, fB[0]);
-      fA[1] = pick(settle(m1), (R)0, fB[1]);
-      fA[2] = pick(settle(m0 | m1), fB[2], (R)0);
-      if constexpr (kMode != kNgp) {
-        rec.hold(sum);
-        R F[4], F2[4];
-        rec.project(P, F, F2);
-        shift_face<R>(E, X, m0, m1, F);
-        if constexpr (kTwo) shift_face<R>(E2, X2, m0, m1, F2);
+      if (part) {
+        const double chiB = fmax(te[2], side);
+        const unsigned long long m0 = ms & __ballot(te[0] > te[1]), m1 = ms & ~m0;
+        R fB[3];
+  #pragma unroll
+        for (int k = 0; k < 3; ++k) fB[k] = (R)1 - absd[k] * (R)(chiB - te[k]);
+        R ngp = 0;   // NGP: the value of the cell being left
+        if constexpr (kMode == kNgp) ngp = point_value<R, Off, kMode>(tv, cell_offset(), P);
+        const bool k2 = te[2] == chiB, k0 = te[0] == chiB, k1 = te[1] == chiB;
+        if (k2) next_layer(2);
+        if (k0) next_layer(0);
+        if (k1) next_layer(1);
+        // the four records of the new exit face, in flight during the integral
+        FaceRecords<R, Off, kMode> rec;
+        if constexpr (kMode != kNgp) {
+          const Off w0 = (k0 ? oX[0] : oE[0]) + (k1 ? oX[1] : oE[1]) + (k2 ? oX[2] : oE[2]);
+          rec.load(tv, w0, k0 ? oX[1] - oE[1] : oX[0] - oE[0], k2 ? oX[1] - oE[1] : oX[2] - oE[2]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const R L = (R)(chiA - chiB);
+        R gB, hB;
+        kernel(chiB, gB, hB);
+        if constexpr (kMode == kNgp) {
+          add_ngp(ngp, chiB, L);
+        } else {
+          const PieceForm<R> q = form_general(Face<R>(E), Face<R>(X), fA, fB);
+          PieceForm<R> q2 = q;
+          if constexpr (kTwo) q2 = form_general(Face<R>(E2), Face<R>(X2), fA, fB);
+          add_piece(q, q2, L, gA, gB, hA, hB, (R)0);
+        }
+        gA = gB;
+        hA = hB;
+        chiA = chiB;
+        fA[0] = pick(settle(m0), (R)0, fB[0]);
+        fA[1] = pick(settle(m1), (R)0, fB[1]);
+        fA[2] = pick(settle(m0 | m1), fB[2], (R)0);
+        if constexpr (kMode != kNgp) {
+          rec.hold(sum);
+          R F[4], F2[4];
+          rec.project(P, F, F2);
+          shift_face<R>(E, X, m0, m1, F);
+          if constexpr (kTwo) shift_face<R>(E2, X2, m0, m1, F2);
+        }
       }
     }
     // ---- one cell of any kind
