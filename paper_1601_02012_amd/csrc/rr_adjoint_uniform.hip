@@ -92,7 +92,7 @@ struct CacheSlot {
   Id tag;         // vertex id, or empty (all bits set)
   float v[6];
 };
-constexpr int kSlots = 256;   // x & 7, y & 7, z & 3
+constexpr int kSlots = 128;   // axis 0 & 7, axes 1 and 2 & 3
 
 template <typename Id>
 __device__ __forceinline__ void flush_slot(float* __restrict__ lam, const CacheSlot<Id>& e) {
@@ -116,7 +116,8 @@ __device__ __forceinline__ void flush_slot(float* __restrict__ lam, const CacheS
 template <typename Id>
 __device__ __forceinline__ void retire_face(float* __restrict__ lam, CacheSlot<Id>* cache,
                                             const float* acc, const float* P, bool mine, int F,
-                                            int W0, int W1, int W2, int n, int lane) {
+                                            int W0, int W1, int W2, int n, const Id* stride,
+                                            int lane) {
   float a[4];
   switch (F) {
     case 0: a[0] = acc[0]; a[1] = acc[2]; a[2] = acc[4]; a[3] = acc[6]; break;
@@ -141,8 +142,8 @@ __device__ __forceinline__ void retire_face(float* __restrict__ lam, CacheSlot<I
   const int by = k == 1 ? sd : (k == 0 ? ia : ib);
   const int bz = k == 2 ? sd : ib;
   const int cx = bx ? X1 : W0, cy = by ? Y1 : W1, cz = bz ? Z1 : W2;
-  const Id my_vid = ((Id)cz * (Id)n + (Id)cy) * (Id)n + (Id)cx;
-  const int my_slot = ((W0 + bx) & 7) | (((W1 + by) & 7) << 3) | (((W2 + bz) & 3) << 6);
+  const Id my_vid = (Id)cx * stride[0] + (Id)cy * stride[1] + (Id)cz * stride[2];
+  const int my_slot = ((W0 + bx) & 7) | (((W1 + by) & 3) << 3) | (((W2 + bz) & 3) << 5);
   const int cb = (lane & 4) ? 3 : 0;
   CacheSlot<Id>& e = cache[my_slot];
   const Id tag = e.tag;
@@ -194,13 +195,36 @@ __device__ __forceinline__ void retire_face(float* __restrict__ lam, CacheSlot<I
   }
 }
 
+// Faces retired by a run along axis 2 (below), kLayers at a time: their corner
+// weights by row (4 layer + corner) and lane.  The sums over the lanes of
+// weight x P are then one 16 x 64 by 64 x 6 product on the matrix cores
+// (v_mfma_f32_16x16x4): a lane reads the weights of row lane % 16 for the 16
+// lanes k = 16 (lane / 16) + s, and holds P of those lanes, component
+// lane % 16, for the whole march.  Rows are padded by a 16-byte chunk so that
+// the sixteen rows start on different banks.
+constexpr int kLayers = 4, kRowPad = 68;
+struct alignas(16) FaceBatch {
+  float w[4 * kLayers][kRowPad];
+};
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// a[i + 2 j] += w N_ij(x, y), the bilinear basis.
+__device__ __forceinline__ void add_point(float* a, float w, float x, float y) {
+  const float y1 = w * y, y0 = w - y1;
+  const float p3 = x * y1, p1 = x * y0;
+  a[0] += y0 - p1;
+  a[1] += p1;
+  a[2] += y1 - p3;
+  a[3] += p3;
+}
+
 // One 8 x 8 tile of rays, all 64 lanes kept active to the end (lanes without
 // a ray, or whose ray has ended, take part in the wavefront reductions with
 // nothing to add).
 template <typename Id>
 __device__ void scatter_tile(const TraceArgs& a, const DevBundle& B, int ix, int iy, int lane,
                              const float* __restrict__ wts, float* __restrict__ lam,
-                             CacheSlot<Id>* cache) {
+                             CacheSlot<Id>* cache, FaceBatch& batch) {
   for (int e = lane; e < kSlots; e += 64) cache[e].tag = (Id)~(Id)0;
   bool alive = ix < B.nx && iy < B.ny;
   const int64_t ray = alive ? (int64_t)iy * B.nx + ix : 0;
@@ -222,9 +246,42 @@ __device__ void scatter_tile(const TraceArgs& a, const DevBundle& B, int ix, int
   projection(RR_Q_KAPPA, d[0], d[1], d[2], Pd);
   float P[6];
 #pragma unroll
-  for (int c = 0; c < 6; ++c) P[c] = (float)Pd[c] * wr;
+  for (int c = 0; c < 6; ++c) P[c] = alive ? (float)Pd[c] * wr : 0.0f;
+  const unsigned long long rays = __ballot(alive);
+  if (rays == 0ull) return;
+  // P of lanes 16 (lane / 16) + s, component lane % 16 (FaceBatch)
+  f32x4 PT[4];
+  {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) batch.w[c][lane] = P[c];
+    __asm__ volatile("" ::: "memory");
+    const int c = lane & 15;
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      PT[s] = c < 6 ? *reinterpret_cast<const f32x4*>(&batch.w[c][(lane & 48) + 4 * s])
+                    : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    __asm__ volatile("" ::: "memory");
+  }
 
   const int n = a.n;
+  // the axes are relabelled cyclically so that axis 2 is the one the tile's
+  // rays run along (the largest component of its first ray)
+  int kz = fabs(d[0]) > fabs(d[2]) ? 0 : 2;
+  kz = fabs(d[1]) > fmax(fabs(d[0]), fabs(d[2])) ? 1 : kz;
+  kz = __builtin_amdgcn_readlane(kz, __builtin_ctzll(rays));
+  const Id vs[3] = {1, (Id)n, (Id)n * (Id)n};
+  const Id stride[3] = {kz == 2 ? vs[0] : (kz == 0 ? vs[1] : vs[2]),
+                        kz == 2 ? vs[1] : (kz == 0 ? vs[2] : vs[0]),
+                        kz == 2 ? vs[2] : (kz == 0 ? vs[0] : vs[1])};
+  const double o[3] = {kz == 2 ? a.o[0] : (kz == 0 ? a.o[1] : a.o[2]),
+                       kz == 2 ? a.o[1] : (kz == 0 ? a.o[2] : a.o[0]),
+                       kz == 2 ? a.o[2] : (kz == 0 ? a.o[0] : a.o[1])};
+  {
+    const double e[3] = {d[0], d[1], d[2]};
+    d[0] = kz == 2 ? e[0] : (kz == 0 ? e[1] : e[2]);
+    d[1] = kz == 2 ? e[1] : (kz == 0 ? e[2] : e[0]);
+    d[2] = kz == 2 ? e[2] : (kz == 0 ? e[0] : e[1]);
+  }
   const double lo = B.chi_lo;
   double chiA = B.chi_hi;
   // per axis: bit k of dpos set when d_k > 0 (the march runs down the lattice)
@@ -235,10 +292,10 @@ __device__ void scatter_tile(const TraceArgs& a, const DevBundle& B, int ix, int
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     r[k] = (d[k] != 0.0) ? 1.0 / d[k] : 0.0;
-    const int m = start_slab(a.o[k], d[k], r[k], chiA, 1.0);
+    const int m = start_slab(o[k], d[k], r[k], chiA, 1.0);
     px[k] = d[k] > 0.0 ? m : m + 1;
-    te[k] = d[k] != 0.0 ? tplane((double)px[k], a.o[k], r[k]) : -__builtin_inf();
-    cpos[k] = a.o[k] - (double)m;
+    te[k] = d[k] != 0.0 ? tplane((double)px[k], o[k], r[k]) : -__builtin_inf();
+    cpos[k] = o[k] - (double)m;
     const int ww = m % n;
     w[k] = ww < 0 ? ww + n : ww;
   }
@@ -253,7 +310,127 @@ __device__ void scatter_tile(const TraceArgs& a, const DevBundle& B, int ix, int
   int64_t count = 0;
   bool stopped = false;   // ended by max_crossings: its open corners still retire
 
+  // kernel times chi_s at chi_A (runs)
+  const float run_scale = (float)(1.0 / (12.0 * B.chi_s));
   while (__ballot(alive) != 0ull) {
+    // ---- run: every ray of the tile is in one cell, has entered it through
+    // axis 2 and leaves it that way.  Each cell adds the transpose of the
+    // piece form's integral (rr_ray.hpp) to its entry and exit face, and the
+    // entry face retires for the whole tile at once.
+    bool part = true;   // the lane takes part in the crossing below
+    if (a.max_crossings <= 0 && __ballot(alive) == rays) {
+      const int first = __builtin_ctzll(rays);
+      const double lim = fmax(fmax(te[0], te[1]), lo);
+      const bool down = (dpos & 4) != 0;
+      const int W0 = __builtin_amdgcn_readlane(w[0], first);
+      const int W1 = __builtin_amdgcn_readlane(w[1], first);
+      const int W2 = __builtin_amdgcn_readlane(w[2], first);
+      const int D = __builtin_amdgcn_readlane(dpos, first);
+      const bool column = w[0] == W0 && w[1] == W1 && dpos == D && te[2] > lim;
+      const bool here = w[2] == W2 && uA[2] == (down ? 1.0f : 0.0f);
+      const bool in_column = (__ballot(column) & rays) == rays;
+      if (in_column && (__ballot(here) & rays) != rays) {
+        // one column of cells, but not one layer of axis 2 (a window that starts
+        // with a plane of axis 0 or 1 across the tile leaves its rays one
+        // crossing apart): those behind cross a face alone, once
+        const int adv = down ? -px[2] : px[2];
+        const int A = __builtin_amdgcn_readlane(adv, first);
+        const unsigned long long ahead = __ballot(adv > A) & rays, level = __ballot(adv == A) & rays;
+        if (ahead != 0ull) part = adv <= A;
+        else if (level != rays) part = adv < A;
+      } else if (in_column) {
+        const bool dn = (D & 4) != 0;   // wavefront-uniform: down for every ray
+        float aE[4], aX[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          aE[v] = dn ? acc[4 + v] : acc[v];
+          aX[v] = dn ? acc[v] : acc[4 + v];
+        }
+        // vertex ids of the face's corners without axis 2
+        Id id01[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int x = (v & 1) ? (W0 + 1 == n ? 0 : W0 + 1) : W0;
+          const int y = (v & 2) ? (W1 + 1 == n ? 0 : W1 + 1) : W1;
+          id01[v] = (Id)x * stride[0] + (Id)y * stride[1];
+        }
+        int zE = dn ? (W2 + 1 == n ? 0 : W2 + 1) : W2;   // entry face's layer
+        int z_first = zE, fill = 0, cells = 0;
+        float gA = (float)chiA * (float)(B.chi_s - chiA);
+        auto flush = [&] {
+          __asm__ volatile("" ::: "memory");
+          f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+          f32x4 A[4];
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+            A[s] = *reinterpret_cast<const f32x4*>(&batch.w[lane & 15][(lane & 48) + 4 * s]);
+#pragma unroll
+          for (int s = 0; s < 16; ++s)
+            sum = __builtin_amdgcn_mfma_f32_16x16x4f32(A[s / 4][s % 4], PT[s / 4][s % 4], sum, 0, 0, 0);
+          __asm__ volatile("" ::: "memory");
+          // lane: component lane % 16 of layer lane / 16, corners 0 .. 3
+          const int g = lane >> 4, c = lane & 15;
+          if (g < fill && c < 6) {
+            int z = dn ? z_first - g : z_first + g;
+            z = z < 0 ? z + n : (z >= n ? z - n : z);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              atomicAdd(lam + (uint64_t)(id01[v] + (Id)z * stride[2]) * 6 + c, sum[v]);
+          }
+          fill = 0;
+        };
+        do {
+          if (alive) {
+            const double chiB = te[2];
+            const float L = (float)(chiA - chiB);
+            const float xB = (float)fma(chiB, d[0], cpos[0]), yB = (float)fma(chiB, d[1], cpos[1]);
+            const float gB = (float)chiB * (float)(B.chi_s - chiB), K = L * L;
+            const float f = L * run_scale;
+            const float s = gA + gB, b = fmaf(0.2f, K, 0.4f * s), t = fmaf(0.6f, K, s);
+            const float k20 = fmaf(2.0f, gA, t) * f, k02 = fmaf(2.0f, gB, t) * f;
+            const float k11 = fmaf(0.4f, K, s) * f;
+            const float dd = (xB - uA[0]) * (yB - uA[1]) * f;
+            const float tE = fmaf(0.2f, gA, b) * dd, tX = fmaf(0.2f, gB, b) * dd;
+            add_point(aE, k20, uA[0], uA[1]);
+            add_point(aE, k11, xB, yB);
+            aE[0] -= tE; aE[1] += tE; aE[2] += tE; aE[3] -= tE;
+            add_point(aX, k11, uA[0], uA[1]);
+            add_point(aX, k02, xB, yB);
+            aX[0] -= tX; aX[1] += tX; aX[2] += tX; aX[3] -= tX;
+            gA = gB;
+            uA[0] = xB;
+            uA[1] = yB;
+            chiA = chiB;
+            px[2] += dn ? -1 : 1;
+            te[2] = tplane((double)px[2], o[2], r[2]);
+          }
+          if (fill == 0) z_first = zE;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            batch.w[4 * fill + v][lane] = aE[v];
+            aE[v] = aX[v];
+            aX[v] = 0.0f;
+          }
+          ++fill;
+          ++cells;
+          zE = dn ? (zE == 0 ? n - 1 : zE - 1) : (zE + 1 == n ? 0 : zE + 1);
+          if (fill == kLayers) flush();
+        } while ((__ballot(te[2] > lim) & rays) == rays);
+        if (fill > 0) flush();
+        // the cell reached: its entry face at zE
+        int z = dn ? zE - 1 : zE;
+        z = z < 0 ? z + n : z;
+        if (alive) {
+          w[2] = z;
+          cpos[2] += dn ? (double)cells : -(double)cells;
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          acc[4 + v] = dn ? aE[v] : aX[v];
+          acc[v] = dn ? aX[v] : aE[v];
+        }
+      }
+    }
     bool stepped[3] = {false, false, false};
     float uB[3] = {0.0f, 0.0f, 0.0f};
     double chiB = lo;
@@ -262,7 +439,7 @@ __device__ void scatter_tile(const TraceArgs& a, const DevBundle& B, int ix, int
     int f0 = -1, f1 = -1;
     int kk = -1;
     bool last = false;
-    if (alive) {
+    if (alive && part) {
       if (count >= maxc) {
         alive = false;
         stopped = true;
@@ -312,7 +489,7 @@ __device__ void scatter_tile(const TraceArgs& a, const DevBundle& B, int ix, int
       const int W1 = __builtin_amdgcn_readlane(w[1], leader);
       const int W2 = __builtin_amdgcn_readlane(w[2], leader);
       const bool mine = f0 == F && w[0] == W0 && w[1] == W1 && w[2] == W2;
-      retire_face<Id>(lam, cache, acc, P, mine, F, W0, W1, W2, n, lane);
+      retire_face<Id>(lam, cache, acc, P, mine, F, W0, W1, W2, n, stride, lane);
       if (mine) {
         f0 = f1;
         f1 = -1;
@@ -323,7 +500,7 @@ __device__ void scatter_tile(const TraceArgs& a, const DevBundle& B, int ix, int
       for (int v = 0; v < 8; ++v) acc[v] = 0.0f;
       stopped = false;
     }
-    if (!alive) continue;
+    if (!alive || !part) continue;
     if (last) {
       alive = false;
       continue;
@@ -353,7 +530,7 @@ __device__ void scatter_tile(const TraceArgs& a, const DevBundle& B, int ix, int
       if (stepped[k]) {
         const bool down = (dpos >> k) & 1;
         px[k] += down ? -1 : 1;
-        te[k] = tplane((double)px[k], a.o[k], r[k]);
+        te[k] = tplane((double)px[k], o[k], r[k]);
         cpos[k] += down ? 1.0 : -1.0;
         uA[k] = 1.0f - uB[k];
         const int s = down ? -1 : 1;
@@ -368,9 +545,10 @@ __device__ void scatter_tile(const TraceArgs& a, const DevBundle& B, int ix, int
 }
 
 template <typename Id>
-__global__ __launch_bounds__(256) void scatter_kernel(TraceArgs a, const float* __restrict__ wts,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void scatter_kernel(TraceArgs a, const float* __restrict__ wts,
                                                       float* __restrict__ lam) {
   __shared__ CacheSlot<Id> cache[4][kSlots];
+  __shared__ FaceBatch batch[4];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int64_t nblk = gridDim.x, blk = blockIdx.x;
@@ -383,7 +561,8 @@ __global__ __launch_bounds__(256) void scatter_kernel(TraceArgs a, const float* 
   const int64_t local = tile - B.tile_begin;
   const int tx = (int)(local % B.tiles_x), ty = (int)(local / B.tiles_x);
   scatter_tile<Id>(a, B, tx * 8 + (lane & 7), ty * 8 + (lane >> 3), lane, wts, lam,
-                   cache[__builtin_amdgcn_readfirstlane(wave)]);
+                   cache[__builtin_amdgcn_readfirstlane(wave)],
+                   batch[__builtin_amdgcn_readfirstlane(wave)]);
 }
 
 // Transpose stencil, built like the forward tensor: a workgroup owns a
