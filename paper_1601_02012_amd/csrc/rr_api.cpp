@@ -488,6 +488,25 @@ int default_block(int64_t n_tiles, int cu_count) {
   return n_tiles <= 4 * (int64_t)cu_count ? 64 : 256;
 }
 
+// Octree march: how far in chi (base cells) a lane may be ahead of where its
+// wavefront stood when the slowest lane last caught up, before it waits.  A lane
+// that goes through refined cells takes up to 16 crossings per base cell; left
+// alone, the lanes of a tile drift apart by whole haloes and share no cache line
+// any more.  The march is bound by its gathers (address unit and L2), so idle
+// lanes cost less than the misses they avoid: 16 bundles of 64^2..384^2 rays over
+// 1..10 degrees through a 96^3 tree of four levels, one persistent launch, 33-42
+// -> 24 ms; 1024^2 rays through a 128^3 tree in the tuner's shape (whose passes
+// split the window in any case) 20.2 -> 18.4 ms.  16 to 72 cells measure alike
+// (24.0-24.7 and 18.0-18.3 ms); at 4 the lanes wait too often (25.1 and 20.3), at
+// 128 they drift (25.8).  With at most two wavefronts per compute unit nothing
+// else fills the machine and the longest wavefront sets the time, so no lane
+// waits: 16 bundles through a 64^3 tree, FP32, 64 tiles 7.35 ms without waiting
+// against 7.85 with, 256 tiles 8.0 against 8.3, 576 tiles 8.3 either way, 1024
+// tiles 9.05 against 8.7, 2304 tiles 10.9 against 9.5.
+double octree_lead(int64_t n_tiles, int cu_count) {
+  return n_tiles <= 2 * (int64_t)cu_count ? INFINITY : 32.0;
+}
+
 // Launch order of the bundles: as given, or (persistent launches)
 // longest-processing-time first, the chi window setting the steps per ray.
 // A stable insertion sort on the caller's index array (no allocation).
@@ -972,6 +991,7 @@ rr_status launch_trace(rr_plan p, rr_tensor t, const rr_trace_params* tp, const 
     a.pieces = pieces;
   }
   a.queue = p->queue;
+  a.lead = octree_lead(tab->n_tiles, p->cu_count);
   const int grid_waves = p->cu_count * waves_per_cu;
   if (block == 0) block = persistent ? 256 : default_block(tab->n_tiles, p->cu_count);
   // A long window can be marched in passes: each pass stops every ray on the
@@ -1158,6 +1178,7 @@ rr_status rr_trace_rays_noalloc(rr_tensor t, const rr_trace_params* tp, const rr
   int dev = 0, cus = 0;
   RR_HIP(hipGetDevice(&dev), "hipGetDevice");
   RR_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "CU count");
+  a.lead = octree_lead(tiles, cus);
   const int grid_waves = cus * 16;
   const int block = persistent ? 256 : default_block(tiles, cus);
   if (persistent) RR_HIP(rr::launch_queue_reset(a.queue, hs), "queue reset");

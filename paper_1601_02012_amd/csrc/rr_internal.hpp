@@ -55,6 +55,9 @@ struct TraceArgs {
   // face at or below pause_chi (base-cell units; -inf: run to chi_lo)
   double* resume;
   double pause_chi;
+  // octree: base cells of chi that a lane may be ahead before it waits for the
+  // others of its wavefront (inf: never waits)
+  double lead;
 };
 
 // Uniform vertex tensor record: 6 components, FP32 (24 B, three 8-byte

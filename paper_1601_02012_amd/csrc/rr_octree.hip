@@ -390,6 +390,14 @@ __device__ __forceinline__ int descend_from(const Tree& T, Off b, int l, const i
 // source-distance moments chi and chi^2 (the many-source walk).
 constexpr int kOctTidal = 0, kOctNgp = 1, kOctSources = 3;
 
+// x of the first active lane, in scalar registers.
+__device__ __forceinline__ double first_lane(double x) {
+  const uint64_t b = (uint64_t)__double_as_longlong(x);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
 // One ray through the octree, in the ray's frame (as the uniform march):
 // per axis the lane keeps, in FP64, the crossing parameter of the current
 // leaf's exit plane and the level-l coordinates m, and the local coordinate
@@ -403,7 +411,7 @@ constexpr int kOctTidal = 0, kOctNgp = 1, kOctSources = 3;
 // A crossing that stays on level 0 or inside the parent oct needs no walk
 // from the base cell.  kOverlap: the next leaf's loads are issued before the
 // integral of the leaf being left (see the target step below).
-template <typename R, bool kDebug, int kMode, typename Off, bool kOverlap>
+template <typename R, bool kDebug, int kMode, typename Off, bool kOverlap, bool kWait>
 __device__ void trace_oct(const Tree& T, const R* __restrict__ cv, const TraceArgs& a,
                           const DevBundle& B, int64_t ray) {
   const int64_t out = B.ray_offset + ray;
@@ -581,10 +589,20 @@ __device__ void trace_oct(const Tree& T, const R* __restrict__ cv, const TraceAr
     }
   };
 
+  double bound = INFINITY;   // wavefront-uniform
   for (;;) {
     if (chiA <= a.pause_chi) {   // the rest of the window is a later pass's
       paused = true;
       break;
+    }
+    // lanes that have come down to `bound` wait until every lane of the
+    // wavefront that still marches has; then all of them go on
+    if constexpr (kWait) {
+      const bool ahead = chiA <= bound;
+      if (__ballot(!ahead) == 0)
+        bound = first_lane(chiA) - a.lead;
+      else if (ahead)
+        continue;
     }
     if (count >= maxc) {
       st = RR_RAY_MAX_STEPS;
@@ -815,7 +833,7 @@ __device__ void trace_oct(const Tree& T, const R* __restrict__ cv, const TraceAr
   }
 }
 
-template <typename R, bool kDebug, int kMode, typename Off, bool kOverlap>
+template <typename R, bool kDebug, int kMode, typename Off, bool kOverlap, bool kWait>
 __device__ __forceinline__ void oct_tile(const Tree& T, const R* cv, const TraceArgs& a,
                                          int64_t tile, int lane) {
   const int b = find_bundle(a.bundles, a.n_bundles, tile);
@@ -824,10 +842,10 @@ __device__ __forceinline__ void oct_tile(const Tree& T, const R* cv, const Trace
   zorder_tile(tile - B.tile_begin, B.tiles_x, B.tiles_y, tx, ty);
   const int ix = tx * 8 + (lane & 7), iy = ty * 8 + (lane >> 3);
   if (ix < B.nx && iy < B.ny)
-    trace_oct<R, kDebug, kMode, Off, kOverlap>(T, cv, a, B, (int64_t)iy * B.nx + ix);
+    trace_oct<R, kDebug, kMode, Off, kOverlap, kWait>(T, cv, a, B, (int64_t)iy * B.nx + ix);
 }
 
-template <typename R, bool kDebug, int kMode, typename Off>
+template <typename R, bool kDebug, int kMode, typename Off, bool kWait>
 __global__ __launch_bounds__(256) void march_octree_kernel(Tree T, const R* __restrict__ cv,
                                                            TraceArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -839,7 +857,7 @@ __global__ __launch_bounds__(256) void march_octree_kernel(Tree T, const R* __re
   if (tile >= a.n_tiles) return;
   // the tidal march computes each integral while the next leaf's corner
   // loads are in flight (the register budget of a direct launch holds them)
-  oct_tile<R, kDebug, kMode, Off, kMode == kOctTidal>(T, cv, a, tile, lane);
+  oct_tile<R, kDebug, kMode, Off, kMode == kOctTidal, kWait>(T, cv, a, tile, lane);
 }
 
 // The FP32 tidal march (no debug outputs, 32-bit offsets) fits 128 VGPRs
@@ -848,7 +866,7 @@ __global__ __launch_bounds__(256) void march_octree_kernel(Tree T, const R* __re
 // 2.34 -> 2.02 s).  The other instantiations spill under that cap.  Under
 // it the loads of the next leaf cannot stay in flight across an integral
 // (the compiler then serialises them), so the integral comes first.
-template <typename R, bool kDebug, int kMode, typename Off>
+template <typename R, bool kDebug, int kMode, typename Off, bool kWait>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
     sizeof(R) == 4 && kMode == 0 && !kDebug && sizeof(Off) == 4 ? 4 : 1)))
 void march_octree_persistent(Tree T, const R* __restrict__ cv, TraceArgs a) {
@@ -857,26 +875,37 @@ void march_octree_persistent(Tree T, const R* __restrict__ cv, TraceArgs a) {
   for (;;) {
     const int64_t tile = next_tile(a.queue, a.n_tiles, q, tried, lane);
     if (tile < 0) break;
-    oct_tile<R, kDebug, kMode, Off, false>(T, cv, a, tile, lane);
+    oct_tile<R, kDebug, kMode, Off, false, kWait>(T, cv, a, tile, lane);
   }
 }
 
-template <typename R, bool kDebug, int kMode, typename Off>
-hipError_t launch_march(const Tree& T, const void* cv, const TraceArgs& a, int persistent,
+template <typename R, bool kDebug, int kMode, typename Off, bool kWait>
+hipError_t launch_one(const Tree& T, const void* cv, const TraceArgs& a, int persistent,
                         int block, int grid_waves, hipStream_t s) {
   if (persistent) {
     const int blocks = (grid_waves + 3) / 4;
-    hipLaunchKernelGGL((march_octree_persistent<R, kDebug, kMode, Off>), dim3(blocks), dim3(256), 0, s, T,
+    hipLaunchKernelGGL((march_octree_persistent<R, kDebug, kMode, Off, kWait>), dim3(blocks), dim3(256), 0, s, T,
                        (const R*)cv, a);
   } else {
     const int wpb = block / 64;
     int64_t blocks = (a.n_tiles + wpb - 1) / wpb;
     if (blocks == 0) return hipSuccess;
     blocks = (blocks + 7) / 8 * 8;
-    hipLaunchKernelGGL((march_octree_kernel<R, kDebug, kMode, Off>), dim3((unsigned)blocks), dim3(block), 0, s,
+    hipLaunchKernelGGL((march_octree_kernel<R, kDebug, kMode, Off, kWait>), dim3((unsigned)blocks), dim3(block), 0, s,
                        T, (const R*)cv, a);
   }
   return hipGetLastError();
+}
+
+// The march that never waits is an instantiation of its own: the test of a
+// lane's lead, though never true, costs the small launches that do without it
+// 4 % (4 bundles of 19^2..57^2 rays in FP64: 5.54 against 5.33 ms).
+template <typename R, bool kDebug, int kMode, typename Off>
+hipError_t launch_march(const Tree& T, const void* cv, const TraceArgs& a, int persistent,
+                        int block, int grid_waves, hipStream_t s) {
+  return a.lead < INFINITY
+             ? launch_one<R, kDebug, kMode, Off, true>(T, cv, a, persistent, block, grid_waves, s)
+             : launch_one<R, kDebug, kMode, Off, false>(T, cv, a, persistent, block, grid_waves, s);
 }
 
 template <typename In, typename Acc>
