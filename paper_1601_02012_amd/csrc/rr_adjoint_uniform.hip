@@ -221,6 +221,14 @@ __device__ __forceinline__ void add_point(float* a, float w, float x, float y) {
 // One 8 x 8 tile of rays, all 64 lanes kept active to the end (lanes without
 // a ray, or whose ray has ended, take part in the wavefront reductions with
 // nothing to add).
+//
+// What bounds it is VALU issue: 211 instructions per crossing and wavefront,
+// 456 while every crossing took the general step with its joint reduction of
+// 24 sums over the wavefront.  A run's crossing forms the piece form's
+// transpose (no Gauss nodes), writes its retired weights to LDS and leaves the
+// reduction to one matrix product per kLayers crossings.  256^3, 1024^2 rays
+// over 5 degrees, 2.8e8 crossings: 2.53 ms (4.0 before; 3.5 with runs but
+// lanes left a layer of axis 2 apart, which keeps a tile out of them).
 template <typename Id>
 __device__ void scatter_tile(const TraceArgs& a, const DevBundle& B, int ix, int iy, int lane,
                              const float* __restrict__ wts, float* __restrict__ lam,

@@ -199,12 +199,14 @@ __device__ __forceinline__ int quad_max(int x) {
 // What bounds it is VALU issue, with the address path of the gathers close
 // behind (an FP32 operation on vector registers takes a SIMD 2.5 clocks, an
 // FP64 one, a compare, a select, an integer minimum or a conversion 4.3, the
-// 4 x 4 matrix instruction 8.6): 120 VALU instructions per crossing and
+// 4 x 4 matrix instruction 8.6): 121 VALU instructions per crossing and
 // wavefront (69 in the run, 175 in a step between runs) against 206 for one
-// loop over cells of any kind with a three-point Gauss rule; address unit 80 %
-// busy.  512^3, 2048^2 rays over 5 degrees: 0.88 ms per segment (1.12 before).
-// Keeping the wavefront in one layer of axis 2 (lanes that leave sideways
-// cross first, the others wait) costs more than it saves: 150 VALU, 0.97 ms.
+// loop over cells of any kind with a three-point Gauss rule; address unit 76 %
+// busy.  512^3, 2048^2 rays over 5 degrees: 0.80 ms per segment (1.12 before;
+// 0.88 while lanes a layer of axis 2 apart were left so, see quad_max).
+// Keeping the wavefront in one layer of axis 2 throughout (lanes that leave
+// sideways cross first, the others wait) cost more than it saved: 150 VALU and
+// 0.97 ms against 0.88.
 template <typename R, bool kDebug, typename Off, int kMode, bool kPass>
 __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const DevBundle& B,
                           int64_t ray, bool own) {
@@ -768,7 +770,8 @@ __device__ __forceinline__ void run_tile(const R* __restrict__ tv, const TraceAr
 // under that cap; FP64 takes what it needs (three: 32 registers spilled, 24.0
 // against 16.0 ms for five 512^3 segments).  Five (96 VGPRs, 14 spilled) gained
 // nothing: 0.95 against 0.89 ms per 512^3 segment of 2048^2 rays; Method A,
-// which spills 8 at four, takes 8.4 ms for five segments against 8.8 at three.
+// which spills 8 at four, took 8.4 ms for five segments against 8.8 at three
+// (both pairs timed before the re-alignment of lanes a layer apart).
 template <typename R, typename Off>
 constexpr int waves_per_simd() {
   return sizeof(R) == 8 ? 1 : (sizeof(Off) == 4 ? 4 : 3);
