@@ -222,8 +222,9 @@ __device__ __forceinline__ void add_point(float* a, float w, float x, float y) {
 // a ray, or whose ray has ended, take part in the wavefront reductions with
 // nothing to add).
 //
-// What bounds it is VALU issue: 211 instructions per crossing and wavefront,
-// 456 while every crossing took the general step with its joint reduction of
+// What bounds it is VALU work (about 45 % of its time at 3.1 clocks each) and
+// the latency of its serial steps (half of the wave cycles wait): 211 VALU
+// instructions per crossing and wavefront, 456 while every crossing took the general step with its joint reduction of
 // 24 sums over the wavefront.  A run's crossing forms the piece form's
 // transpose (no Gauss nodes), writes its retired weights to LDS and leaves the
 // reduction to one matrix product per kLayers crossings.  256^3, 1024^2 rays
