@@ -298,6 +298,11 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
   const Off up = down2 ? (Off)0 : ~(Off)0;
   const Off cx = down2 ? (Off)0 : span2 + (Off)1;
   const double step2 = down2 ? -1.0 : 1.0;
+  // whether the lanes of every quad march axis 2 in one sense: only then do
+  // equally many crossings along it mean the same layer, and may a quad share
+  // its records or wait for its slowest lane (rays of a bundle are free to
+  // look either way).  A lane that is missing here never marches.
+  const bool one_way = __ballot(quad_first((uint32_t)down2) == (uint32_t)down2) == ~0ull;
 
   constexpr bool kTwo = kMode == kMethodA;   // a second set of corner values (n . grad Phi)
   // corner values c = i_0 + 2 i_1 of the entry and the exit face of axis 2
@@ -446,6 +451,7 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
       // and share its frame
       bool run = __ballot(te[2] > lim) == all, part = true;
       if constexpr (sizeof(R) == 4 && kMode != kNgp) {
+        run = run && one_way;
         if (run) {
           const Off w2 = oX[0] + oX[1];
           run = (__ballot(quad_first(w01) == w01) & __ballot(quad_first(w2) == w2)) == ~0ull;
