@@ -192,9 +192,11 @@ __device__ __forceinline__ int quad_max(int x) {
 // instead of four, shared within quads and projected on the matrix cores.
 // Between runs every lane crosses one face at a time with the loads of the new
 // face in flight during the integral; what neither covers (edges, ends of the
-// window, sources, open grids, debug outputs, crossing limits) takes the cell
-// of any kind at the bottom.  All three round a piece alike, so a ray's result
-// depends neither on its neighbours nor on the launch.
+// window, sources) takes the cell of any kind at the bottom.  All three round a
+// piece alike, so a ray's result depends neither on its neighbours nor on the
+// launch.  Launches that follow every crossing (debug outputs, crossing limits)
+// or may end at the edge of an open grid are instantiations without runs
+// (kRun false, launch_off).
 //
 // What bounds it is VALU issue, with the address path of the gathers close
 // behind (an FP32 operation on vector registers takes a SIMD 2.5 clocks, an
@@ -207,7 +209,7 @@ __device__ __forceinline__ int quad_max(int x) {
 // Keeping the wavefront in one layer of axis 2 throughout (lanes that leave
 // sideways cross first, the others wait) cost more than it saved: 150 VALU and
 // 0.97 ms against 0.88.
-template <typename R, bool kDebug, typename Off, int kMode, bool kPass>
+template <typename R, bool kDebug, typename Off, int kMode, bool kPass, bool kRun>
 __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const DevBundle& B,
                           int64_t ray, bool own) {
   const int64_t out = B.ray_offset + ray;
@@ -360,8 +362,16 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
   int64_t count = 0;
   int32_t st = RR_RAY_OK;
   const int64_t maxc = a.max_crossings > 0 ? a.max_crossings : INT64_MAX;
-  // the run along axis 2 keeps no count, hash or domain test
-  const bool may_run = !kDebug && !a.open && a.max_crossings <= 0;
+  static_assert(!(kDebug && kRun), "runs keep no count, hash or log");
+  // open grids: chi of the last plane whose crossing leads into a cell with a
+  // whole stencil (cells 2 .. n - 3 on every axis)
+  double open_halt = -INFINITY;
+  if (!kRun && a.open) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      if (d[k] != 0.0)
+        open_halt = fmax(open_halt, tplane(d[k] > 0.0 ? 2.0 : (double)(n - 2), o[k], r[k]));
+  }
 
   // the kernel at chi: g times chi_s (tidal), chi (sources), both g and
   // dg/dchi times chi_s (Method A)
@@ -432,25 +442,53 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
     return low;
   };
 
+  // what a debug launch writes of the piece that ends at chiB
+  auto record_piece = [&](double chiB) {
+    if constexpr (kDebug) {
+      // cell id = vertex id of its lower corner
+      const int64_t cell = (int64_t)(cell_offset() / kRec);
+      if (a.hash) hv = fnv_piece(hv, cell, chiA, chiB);
+      if (own && a.log && count < a.log_stride) {
+        LogRecord* L0 = reinterpret_cast<LogRecord*>(a.log) + out * a.log_stride + count;
+        L0->cell = cell;
+        L0->chi_a = chiA;
+        L0->chi_b = chiB;
+      }
+    }
+  };
+
   for (;;) {
+    if (!kRun && a.open) {
+      bool outside = false;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const double m = r[k] > 0.0 ? pp[k] : pp[k] - 1.0;
+        outside |= m < 2.0 || m > (double)(n - 3);
+      }
+      if (outside) {
+        st = RR_RAY_OUT_OF_DOMAIN;
+        break;
+      }
+    }
     // the walk stops at chi_lo, or at the next source distance above it; a
     // pass also before its boundary
     double stop = lo;
     if constexpr (kMode == kSources) stop = src_j >= lo ? src_j : lo;
     // (Method A's first piece carries a surface term)
-    const bool go = may_run && (!kTwo || chiA < B.chi_hi);
+    const bool first = kTwo && !(chiA < B.chi_hi);
     const unsigned long long all = __ballot(1);
     double halt = stop;
-    if constexpr (kPass) halt = fmax(stop, a.pause_chi);
-    while (__ballot(go) == all) {
+    if constexpr (kPass) halt = fmax(halt, a.pause_chi);
+    if constexpr (!kRun) halt = fmax(halt, open_halt);
+    while (__ballot(!first && (kRun || count < maxc)) == all) {
       const double side = fmax(te[0], te[1]);
       const double lim = fmax(side, halt);
       const Off w01 = oE[0] + oE[1];
       // one record per lane: all 64 lanes march (matrix instructions ignore
       // the execution mask), and the four lanes of every quad are in one cell
       // and share its frame
-      bool run = __ballot(te[2] > lim) == all, part = true;
-      if constexpr (sizeof(R) == 4 && kMode != kNgp) {
+      bool run = kRun && __ballot(te[2] > lim) == all, part = true;
+      if constexpr (kRun && sizeof(R) == 4 && kMode != kNgp) {
         run = run && one_way;
         if (run) {
           const Off w2 = oX[0] + oX[1];
@@ -469,7 +507,8 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
       }
       if (run) {
         // ---- every lane leaves its cell through axis 2 alone
-        if constexpr (kMode == kNgp) {
+        if constexpr (!kRun) {
+        } else if constexpr (kMode == kNgp) {
           do {
             const R Qc = point_value<R, Off, kMode>(tv, cell_offset(), P);
             add_ngp(Qc, te[2], (R)(chiA - te[2]));
@@ -579,6 +618,8 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
         for (int k = 0; k < 3; ++k) fB[k] = (R)1 - absd[k] * (R)(chiB - te[k]);
         R ngp = 0;   // NGP: the value of the cell being left
         if constexpr (kMode == kNgp) ngp = point_value<R, Off, kMode>(tv, cell_offset(), P);
+        record_piece(chiB);
+        if constexpr (!kRun) ++count;
         const bool k2 = te[2] == chiB, k0 = te[0] == chiB, k1 = te[1] == chiB;
         if (k2) next_layer(2);
         if (k0) next_layer(0);
@@ -617,18 +658,6 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
       }
     }
     // ---- one cell of any kind
-    if (a.open) {
-      bool outside = false;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const double m = r[k] > 0.0 ? pp[k] : pp[k] - 1.0;
-        outside |= m < 2.0 || m > (double)(n - 3);
-      }
-      if (outside) {
-        st = RR_RAY_OUT_OF_DOMAIN;
-        break;
-      }
-    }
     if constexpr (kPass) {
       if (chiA <= a.pause_chi) break;   // the rest of the window is a later pass's
     }
@@ -667,17 +696,7 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
     }
     gA = gB;
     hA = hB;
-    if constexpr (kDebug) {
-      // cell id = vertex id of its lower corner
-      const int64_t cell = (int64_t)(cell_offset() / kRec);
-      if (a.hash) hv = fnv_piece(hv, cell, chiA, chiB);
-      if (own && a.log && count < a.log_stride) {
-        LogRecord* L0 = reinterpret_cast<LogRecord*>(a.log) + out * a.log_stride + count;
-        L0->cell = cell;
-        L0->chi_a = chiA;
-        L0->chi_b = chiB;
-      }
-    }
+    record_piece(chiB);
     ++count;
     if constexpr (kMode == kSources) {
       if (src_j == chiB) {
@@ -751,7 +770,7 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
   }
 }
 
-template <typename R, bool kDebug, typename Off, int kMode, bool kPass>
+template <typename R, bool kDebug, typename Off, int kMode, bool kPass, bool kRun>
 __device__ __forceinline__ void run_tile(const R* __restrict__ tv, const TraceArgs& a,
                                          int64_t tile, int lane) {
   const int b = find_bundle(a.bundles, a.n_bundles, tile);
@@ -768,7 +787,7 @@ __device__ __forceinline__ void run_tile(const R* __restrict__ tv, const TraceAr
   const bool own = ix < B.nx && iy < B.ny;
   ix = min(ix, B.nx - 1);
   iy = min(iy, B.ny - 1);
-  trace_one<R, kDebug, Off, kMode, kPass>(tv, a, B, (int64_t)iy * B.nx + ix, own);
+  trace_one<R, kDebug, Off, kMode, kPass, kRun>(tv, a, B, (int64_t)iy * B.nx + ix, own);
 }
 
 // Wavefronts per SIMD that the register budget is held to: four (128 VGPRs)
@@ -777,16 +796,19 @@ __device__ __forceinline__ void run_tile(const R* __restrict__ tv, const TraceAr
 // against 16.0 ms for five 512^3 segments).  Five (96 VGPRs, 14 spilled) gained
 // nothing: 0.95 against 0.89 ms per 512^3 segment of 2048^2 rays; Method A,
 // which spills 8 at four, took 8.4 ms for five segments against 8.8 at three
-// (both pairs timed before the re-alignment of lanes a layer apart).
-template <typename R, typename Off>
+// (both pairs timed before the re-alignment of lanes a layer apart).  Without
+// runs: four as well, and what they need for the others (FP32 at five 0.6 of the
+// speed, FP64 at three 0.8 to 1).
+template <typename R, typename Off, bool kRun>
 constexpr int waves_per_simd() {
+  if (!kRun) return sizeof(R) == 4 && sizeof(Off) == 4 ? 4 : 1;
   return sizeof(R) == 8 ? 1 : (sizeof(Off) == 4 ? 4 : 3);
 }
 
 // One wavefront per tile.  Workgroups are dealt round-robin to the 8 XCDs;
 // remap so that XCD x gets the x-th contiguous slice of tiles.
-template <typename R, bool kDebug, typename Off, int kMode, bool kPass>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_simd<R, Off>())))
+template <typename R, bool kDebug, typename Off, int kMode, bool kPass, bool kRun>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_simd<R, Off, kRun>())))
 void march_uniform_kernel(const R* __restrict__ tv, TraceArgs a) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -798,22 +820,22 @@ void march_uniform_kernel(const R* __restrict__ tv, TraceArgs a) {
   // the tile is the same for the 64 lanes: keep it (and the bundle) scalar
   const int64_t tile = vblk * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(wave);
   if (tile >= a.n_tiles) return;
-  run_tile<R, kDebug, Off, kMode, kPass>(tv, a, tile, lane);
+  run_tile<R, kDebug, Off, kMode, kPass, kRun>(tv, a, tile, lane);
 }
 
 // Persistent workgroups: every wavefront pulls tiles from its chiplet's
 // counter, then from the others', until all are drained (every wave reaches
 // the exit test).  The tile is the same for the 64 lanes: it (and the
 // bundle) stays scalar.
-template <typename R, bool kDebug, typename Off, int kMode, bool kPass>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_simd<R, Off>())))
+template <typename R, bool kDebug, typename Off, int kMode, bool kPass, bool kRun>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_per_simd<R, Off, kRun>())))
 void march_uniform_persistent(const R* __restrict__ tv, TraceArgs a) {
   const int lane = threadIdx.x & 63;
   int q = blockIdx.x % kQueues, tried = 0;
   for (;;) {
     const int64_t tile = next_tile(a.queue, a.n_tiles, q, tried, lane);
     if (tile < 0) break;
-    run_tile<R, kDebug, Off, kMode, kPass>(tv, a, tile, lane);
+    run_tile<R, kDebug, Off, kMode, kPass, kRun>(tv, a, tile, lane);
   }
 }
 
@@ -880,37 +902,50 @@ __global__ __launch_bounds__(256) void kappa_from_pieces_kernel(const R* __restr
   }
 }
 
-template <typename R, bool kDebug, typename Off, int kMode, bool kPass>
+template <typename R, bool kDebug, typename Off, int kMode, bool kPass, bool kRun>
 hipError_t launch3(const void* tv, const TraceArgs& a, int persistent, int block, int grid_waves,
                    hipStream_t s) {
   const int wpb = block / 64;
   if (persistent) {
     const int blocks = (grid_waves + wpb - 1) / wpb;
-    hipLaunchKernelGGL((march_uniform_persistent<R, kDebug, Off, kMode, kPass>), dim3(blocks), dim3(block), 0, s,
+    hipLaunchKernelGGL((march_uniform_persistent<R, kDebug, Off, kMode, kPass, kRun>), dim3(blocks), dim3(block), 0, s,
                        (const R*)tv, a);
   } else {
     int64_t blocks = (a.n_tiles + wpb - 1) / wpb;
     if (blocks == 0) return hipSuccess;
     blocks = (blocks + 7) / 8 * 8;   // the XCD remap is a bijection on multiples of 8
-    hipLaunchKernelGGL((march_uniform_kernel<R, kDebug, Off, kMode, kPass>), dim3((unsigned)blocks), dim3(block),
+    hipLaunchKernelGGL((march_uniform_kernel<R, kDebug, Off, kMode, kPass, kRun>), dim3((unsigned)blocks), dim3(block),
                        0, s, (const R*)tv, a);
   }
   return hipGetLastError();
 }
 
+// Runs keep no count and test no domain, so launches with debug outputs, a
+// crossing limit or an open grid cannot use them, and pay for the registers
+// they hold where they are compiled in: 256^3 open grid, 1400^2 rays over 8
+// degrees, Method A in FP64 2.95 ms with runs compiled in and each cell taken as
+// one of any kind, 2.09 without runs and single faces crossed as between them;
+// FP32 kappa off the axes 1.90 against 1.82.
+template <typename R, typename Off, int kMode>
+hipError_t launch_off(const void* tv, const TraceArgs& a, int persistent, int block,
+                      int grid_waves, hipStream_t s) {
+  const bool dbg = a.hash || a.log || a.count;
+  const bool run = !a.open && a.max_crossings <= 0;
+  // split marches never carry debug outputs (the host keeps those in one pass)
+  if (a.resume)
+    return run ? launch3<R, false, Off, kMode, true, true>(tv, a, persistent, block, grid_waves, s)
+               : launch3<R, false, Off, kMode, true, false>(tv, a, persistent, block, grid_waves, s);
+  if (dbg)
+    return launch3<R, true, Off, kMode, false, false>(tv, a, persistent, block, grid_waves, s);
+  return run ? launch3<R, false, Off, kMode, false, true>(tv, a, persistent, block, grid_waves, s)
+             : launch3<R, false, Off, kMode, false, false>(tv, a, persistent, block, grid_waves, s);
+}
+
 template <typename R, int kMode>
 hipError_t launch_mode(const void* tv, const TraceArgs& a, bool small, int persistent, int block,
                        int grid_waves, hipStream_t s) {
-  const bool dbg = a.hash || a.log || a.count;
-  // split marches never carry debug outputs (the host keeps those in one pass)
-  if (a.resume)
-    return small ? launch3<R, false, uint32_t, kMode, true>(tv, a, persistent, block, grid_waves, s)
-                 : launch3<R, false, uint64_t, kMode, true>(tv, a, persistent, block, grid_waves, s);
-  if (dbg)
-    return small ? launch3<R, true, uint32_t, kMode, false>(tv, a, persistent, block, grid_waves, s)
-                 : launch3<R, true, uint64_t, kMode, false>(tv, a, persistent, block, grid_waves, s);
-  return small ? launch3<R, false, uint32_t, kMode, false>(tv, a, persistent, block, grid_waves, s)
-               : launch3<R, false, uint64_t, kMode, false>(tv, a, persistent, block, grid_waves, s);
+  return small ? launch_off<R, uint32_t, kMode>(tv, a, persistent, block, grid_waves, s)
+               : launch_off<R, uint64_t, kMode>(tv, a, persistent, block, grid_waves, s);
 }
 
 template <typename R>
