@@ -614,7 +614,7 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
         const double chiB = fmax(te[2], side);
         const unsigned long long m0 = ms & __ballot(te[0] > te[1]), m1 = ms & ~m0;
         R fB[3];
-  #pragma unroll
+#pragma unroll
         for (int k = 0; k < 3; ++k) fB[k] = (R)1 - absd[k] * (R)(chiB - te[k]);
         R ngp = 0;   // NGP: the value of the cell being left
         if constexpr (kMode == kNgp) ngp = point_value<R, Off, kMode>(tv, cell_offset(), P);
@@ -645,15 +645,15 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
         gA = gB;
         hA = hB;
         chiA = chiB;
-        fA[0] = pick(settle(m0), (R)0, fB[0]);
-        fA[1] = pick(settle(m1), (R)0, fB[1]);
-        fA[2] = pick(settle(m0 | m1), fB[2], (R)0);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) fA[k] = fB[k];
+        enter_cell(fA, m0, m1);
         if constexpr (kMode != kNgp) {
           rec.hold(sum);
           R F[4], F2[4];
           rec.project(P, F, F2);
-          shift_face<R>(E, X, m0, m1, F);
-          if constexpr (kTwo) shift_face<R>(E2, X2, m0, m1, F2);
+          shift_face(E, X, m0, m1, F);
+          if constexpr (kTwo) shift_face(E2, X2, m0, m1, F2);
         }
       }
     }
@@ -739,8 +739,8 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
       R F[4], F2[4];
       load_face<R, Off, kMode>(tv, w0, da, db, P, F, F2);
       const unsigned long long m0 = __ballot(k0), m1 = __ballot(k1);
-      shift_face<R>(E, X, m0, m1, F);
-      if constexpr (kTwo) shift_face<R>(E2, X2, m0, m1, F2);
+      shift_face(E, X, m0, m1, F);
+      if constexpr (kTwo) shift_face(E2, X2, m0, m1, F2);
     } else {
       load_cell();
     }

@@ -179,25 +179,73 @@ __device__ __forceinline__ void cell_moments(const R* q, const R* uA, const R* u
   mb = b * L;
 }
 
-// t where the lane's bit of m is set, else f.  The mask is read from a pair of
-// scalar registers: a row of selects on VCC in the short encoding takes the
-// SIMD 23 clocks each, this form 4.  A mask goes through settle() first: two
-// wait states are due between the compare that writes it and a select that
-// reads it, and the compiler does not count them for these statements.
-__device__ __forceinline__ unsigned long long settle(unsigned long long m) {
-  asm volatile("s_nop 1" : "+s"(m));
-  return m;
+// Selects by lane masks held in pairs of scalar registers: a row of selects on
+// VCC in the short encoding takes the SIMD 23 clocks each, this form 4.  Each
+// statement opens with the two wait states due between a vector instruction
+// that writes a mask (a compare, the reload of a spilled one) and a select that
+// reads it: the compiler does not count them for hand-written statements, and
+// inside one it can put nothing between.
+
+// The entry face's values E and the exit face's X[0..2], in place: see
+// shift_face (m01 = m0 | m1).
+__device__ __forceinline__ void shift_words(float* E, float* X, unsigned long long m0,
+                                            unsigned long long m1, unsigned long long m01,
+                                            const float* F) {
+  asm("s_nop 1\n\t"
+      "v_cndmask_b32_e64 %0, %4, %2, %12\n\t"
+      "v_cndmask_b32_e64 %0, %0, %1, %11\n\t"
+      "v_cndmask_b32_e64 %1, %5, %3, %12\n\t"
+      "v_cndmask_b32_e64 %1, %1, %8, %11\n\t"
+      "v_cndmask_b32_e64 %4, %8, %6, %12\n\t"
+      "v_cndmask_b32_e64 %4, %4, %5, %11\n\t"
+      "v_cndmask_b32_e64 %5, %9, %7, %12\n\t"
+      "v_cndmask_b32_e64 %5, %5, %10, %11\n\t"
+      "v_cndmask_b32_e64 %2, %6, %8, %12\n\t"
+      "v_cndmask_b32_e64 %2, %2, %3, %11\n\t"
+      "v_cndmask_b32_e64 %3, %7, %9, %13\n\t"
+      "v_cndmask_b32_e64 %6, %10, %7, %11"
+      : "+&v"(E[0]), "+&v"(E[1]), "+&v"(E[2]), "+&v"(E[3]), "+&v"(X[0]), "+&v"(X[1]), "+&v"(X[2])
+      : "v"(X[3]), "v"(F[0]), "v"(F[1]), "v"(F[2]), "s"(m0), "s"(m1), "s"(m01));
 }
-__device__ __forceinline__ float pick(unsigned long long m, float t, float f) {
-  float v;
-  asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(v) : "v"(f), "v"(t), "s"(m));
-  return v;
+
+// x where the lane's bit of m is clear, 0 where it is set (y, z likewise).
+__device__ __forceinline__ void clear_words(float& x, float& y, float& z, unsigned long long mx,
+                                            unsigned long long my, unsigned long long mz) {
+  asm("s_nop 1\n\t"
+      "v_cndmask_b32_e64 %0, %0, 0, %3\n\t"
+      "v_cndmask_b32_e64 %1, %1, 0, %4\n\t"
+      "v_cndmask_b32_e64 %2, %2, 0, %5"
+      : "+&v"(x), "+&v"(y), "+&v"(z)
+      : "s"(mx), "s"(my), "s"(mz));
 }
-__device__ __forceinline__ double pick(unsigned long long m, double t, double f) {
-  const uint64_t tb = (uint64_t)__double_as_longlong(t), fb = (uint64_t)__double_as_longlong(f);
-  const float lo = pick(m, __uint_as_float((uint32_t)tb), __uint_as_float((uint32_t)fb));
-  const float hi = pick(m, __uint_as_float((uint32_t)(tb >> 32)), __uint_as_float((uint32_t)(fb >> 32)));
-  return __hiloint2double(__float_as_int(hi), __float_as_int(lo));
+
+// The two halves of doubles.
+template <int kN>
+__device__ __forceinline__ void split_words(const double* v, float* lo, float* hi) {
+#pragma unroll
+  for (int c = 0; c < kN; ++c) {
+    lo[c] = __int_as_float(__double2loint(v[c]));
+    hi[c] = __int_as_float(__double2hiint(v[c]));
+  }
+}
+template <int kN>
+__device__ __forceinline__ void join_words(const float* lo, const float* hi, double* v) {
+#pragma unroll
+  for (int c = 0; c < kN; ++c) v[c] = __hiloint2double(__float_as_int(hi[c]), __float_as_int(lo[c]));
+}
+
+// f of a lane that has crossed one face, along axis 0 in the lanes of m0, axis 1
+// in those of m1 and axis 2 in the others: 0 on that axis.
+__device__ __forceinline__ void enter_cell(float* f, unsigned long long m0, unsigned long long m1) {
+  clear_words(f[0], f[1], f[2], m0, m1, ~(m0 | m1));
+}
+__device__ __forceinline__ void enter_cell(double* f, unsigned long long m0,
+                                           unsigned long long m1) {
+  float lo[3], hi[3];
+  split_words<3>(f, lo, hi);
+  enter_cell(lo, m0, m1);
+  enter_cell(hi, m0, m1);
+  join_words<3>(lo, hi, f);
 }
 
 // Corner values q[i + 2 j] of one face and its bilinear coefficients
@@ -317,21 +365,22 @@ __device__ __forceinline__ R integrate_constant(const PieceForm<R>& f) {
 // axis 2 in the others: the four values of that face move to the entry side,
 // the four of the new exit face F_j (j = i_a + 2 i_b over the two other axes
 // a < b) come in.
-template <typename R>
-__device__ __forceinline__ void shift_face(R* E, R* X, unsigned long long m0,
-                                           unsigned long long m1, const R* F) {
-  m0 = settle(m0);
-  m1 = settle(m1);
-  const unsigned long long m01 = m0 | m1;
-  const R e0 = pick(m0, E[1], pick(m1, E[2], X[0]));
-  const R e1 = pick(m0, F[0], pick(m1, E[3], X[1]));
-  const R e2 = pick(m0, E[3], pick(m1, F[0], X[2]));
-  const R e3 = pick(m01, F[1], X[3]);
-  const R x0 = pick(m0, X[1], pick(m1, X[2], F[0]));
-  const R x1 = pick(m0, F[2], pick(m1, X[3], F[1]));
-  const R x2 = pick(m0, X[3], F[2]);
-  E[0] = e0; E[1] = e1; E[2] = e2; E[3] = e3;
-  X[0] = x0; X[1] = x1; X[2] = x2; X[3] = F[3];
+__device__ __forceinline__ void shift_face(float* E, float* X, unsigned long long m0,
+                                           unsigned long long m1, const float* F) {
+  shift_words(E, X, m0, m1, m0 | m1, F);
+  X[3] = F[3];
+}
+__device__ __forceinline__ void shift_face(double* E, double* X, unsigned long long m0,
+                                           unsigned long long m1, const double* F) {
+  float El[4], Eh[4], Xl[4], Xh[4], Fl[3], Fh[3];
+  split_words<4>(E, El, Eh);
+  split_words<4>(X, Xl, Xh);
+  split_words<3>(F, Fl, Fh);
+  shift_words(El, Xl, m0, m1, m0 | m1, Fl);
+  shift_words(Eh, Xh, m0, m1, m0 | m1, Fh);
+  join_words<4>(El, Eh, E);
+  join_words<3>(Xl, Xh, X);
+  X[3] = F[3];
 }
 
 // FNV-1a, 64 bit, over the 8 little-endian bytes of w.
