@@ -395,11 +395,11 @@ __device__ void trace_one(const R* __restrict__ tv, const TraceArgs& a, const De
     } else if constexpr (kMode == kSources) {
       // the moments' kernels chi and chi^2 (curvature -L^2)
       const R Ls = scaled(L);
-      ic = integrate_form(q, gA, gB, (R)0) * Ls;
+      ic = integrate_form(q, gA, gB) * Ls;
       ic2 = integrate_form(q, gA * gA, gB * gB, -(L * L)) * Ls;
     } else {
       R s = integrate_form(q, gA, gB, L * L);
-      if constexpr (kMode == kMethodA) s += integrate_form(q2, hA, hB, (R)0);
+      if constexpr (kMode == kMethodA) s += integrate_form(q2, hA, hB);
       ic = scaled(fma(s, L, surface));
     }
     if constexpr (sizeof(R) == 4) {

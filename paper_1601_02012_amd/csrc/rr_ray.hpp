@@ -355,6 +355,15 @@ __device__ __forceinline__ R integrate_form(const PieceForm<R>& f, R gA, R gB, R
   return fma(f.u0, k20, fma(f.m, k11, fma(f.u1, k02, -fma(f.cA, h21, f.cB * h12))));
 }
 
+// The same with K = 0.
+template <typename R>
+__device__ __forceinline__ R integrate_form(const PieceForm<R>& f, R gA, R gB) {
+  const R s = gA + gB, b = (R)0.4 * s;
+  const R k20 = fma((R)2, gA, s), k02 = fma((R)2, gB, s);
+  const R h21 = fma((R)0.2, gA, b), h12 = fma((R)0.2, gB, b);
+  return fma(f.u0, k20, fma(f.m, s, fma(f.u1, k02, -fma(f.cA, h21, f.cB * h12))));
+}
+
 // 12 int_0^1 Q dt.
 template <typename R>
 __device__ __forceinline__ R integrate_constant(const PieceForm<R>& f) {
