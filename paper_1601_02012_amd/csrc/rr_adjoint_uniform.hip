@@ -327,15 +327,18 @@ __device__ void scatter_tile(const TraceArgs& a, const DevBundle& B, int ix, int
     // piece form's integral (rr_ray.hpp) to its entry and exit face, and the
     // entry face retires for the whole tile at once.
     bool part = true;   // the lane takes part in the crossing below
-    if (a.max_crossings <= 0 && __ballot(alive) == rays) {
+    // Off the axes most crossings fail the first test, the exit through axis 2,
+    // and pay for no more than it (255 x 195 rays off the axes through 48^3 cells
+    // 1.136 -> 1.075 ms).
+    const double lim = fmax(fmax(te[0], te[1]), lo);
+    if (a.max_crossings <= 0 && (__ballot(alive && te[2] > lim) & rays) == rays) {
       const int first = __builtin_ctzll(rays);
-      const double lim = fmax(fmax(te[0], te[1]), lo);
       const bool down = (dpos & 4) != 0;
       const int W0 = __builtin_amdgcn_readlane(w[0], first);
       const int W1 = __builtin_amdgcn_readlane(w[1], first);
       const int W2 = __builtin_amdgcn_readlane(w[2], first);
       const int D = __builtin_amdgcn_readlane(dpos, first);
-      const bool column = w[0] == W0 && w[1] == W1 && dpos == D && te[2] > lim;
+      const bool column = w[0] == W0 && w[1] == W1 && dpos == D;
       const bool here = w[2] == W2 && uA[2] == (down ? 1.0f : 0.0f);
       const bool in_column = (__ballot(column) & rays) == rays;
       if (in_column && (__ballot(here) & rays) != rays) {
