@@ -479,13 +479,28 @@ rr_status validate_trace(rr_tensor t, const rr_trace_params* tp, const rr_bundle
   return RR_OK;
 }
 
-// Workgroup size of a one-wavefront-per-tile launch that no plan has tuned:
-// with at most four wavefronts per compute unit each gets a workgroup of its
-// own, so that all units work (four to a workgroup would leave three quarters of
-// them idle); more tiles go four to a workgroup, neighbours sharing an L1.
-// 128^2 rays through 64^3 cells in FP64 (256 tiles): 44 -> 33 us.
-int default_block(int64_t n_tiles, int cu_count) {
-  return n_tiles <= 4 * (int64_t)cu_count ? 64 : 256;
+// Workgroup size of a one-wavefront-per-tile launch that no plan has tuned.  Up
+// to `alone` wavefronts per compute unit each gets a workgroup of its own, so that
+// all units work (four to a workgroup would leave three quarters of them idle at
+// one per unit); more tiles go four to a workgroup, neighbours sharing an L1.
+// Time at four to a workgroup over time at one, 192^3 cells (octree: 48^3 of four
+// levels), maps along and off the axes over 1.5 and 6 degrees, 256 units:
+//   tiles                  16 - 256     384 - 512     576 - 768    896 - 1024
+//   FP64 tidal           0.98 - 1.26   0.97 - 1.18   0.97 - 1.17   0.95 - 1.05
+//   other uniform        0.96 - 1.08   0.88 - 1.05   0.93 - 1.04   0.94 - 1.06
+//   octree               1.00 - 1.08   0.93 - 1.04   0.95 - 1.01   0.99 - 1.01
+//   adjoint              1.01 - 1.06   0.98 - 1.06   0.98 - 1.03   0.87 - 1.01
+// The FP64 tidal march (twelve 16-byte loads per crossing and lane) gains up to
+// three per unit along the axes (1.04 to 1.18) and is even off them, the adjoint
+// up to two; the others only lose beyond one.
+int default_block(int64_t n_tiles, int alone, int cu_count) {
+  return n_tiles <= alone * (int64_t)cu_count ? 64 : 256;
+}
+constexpr int kAloneAdjoint = 2;
+int alone_march(rr_tensor t, int mode) {
+  const bool tidal64 = t->kind == RR_GRID_UNIFORM && t->precision == RR_PREC_FP64 &&
+                       (mode == 0 || mode == 3);
+  return tidal64 ? 3 : 1;
 }
 
 // Octree march: how far in chi (base cells) a lane may be ahead of where its
@@ -993,7 +1008,7 @@ rr_status launch_trace(rr_plan p, rr_tensor t, const rr_trace_params* tp, const 
   a.queue = p->queue;
   a.lead = octree_lead(tab->n_tiles, p->cu_count);
   const int grid_waves = p->cu_count * waves_per_cu;
-  if (block == 0) block = persistent ? 256 : default_block(tab->n_tiles, p->cu_count);
+  if (block == 0) block = persistent ? 256 : default_block(a.n_tiles, alone_march(t, a.mode), p->cu_count);
   // A long window can be marched in passes: each pass stops every ray on the
   // first face at or below the pass's chi boundary and the next pass resumes
   // on that face (the same pieces in the same order: the results are
@@ -1095,7 +1110,7 @@ rr_status rr_trace_rays_adjoint(rr_plan p, rr_tensor t, const rr_field_desc* f,
   a.quantity = RR_Q_KAPPA;
   a.max_crossings = tp->max_crossings;
   RR_HIP(rr::launch_adjoint_uniform(a, dl_dkappa, (float*)t->grad, dl_dphi,
-                                    default_block(tab->n_tiles, p->cu_count), hs),
+                                    default_block(a.n_tiles, kAloneAdjoint, p->cu_count), hs),
          "adjoint launch");
   return table_used(tab, hs);
 }
@@ -1180,7 +1195,7 @@ rr_status rr_trace_rays_noalloc(rr_tensor t, const rr_trace_params* tp, const rr
   RR_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "CU count");
   a.lead = octree_lead(tiles, cus);
   const int grid_waves = cus * 16;
-  const int block = persistent ? 256 : default_block(tiles, cus);
+  const int block = persistent ? 256 : default_block(a.n_tiles, alone_march(t, a.mode), cus);
   if (persistent) RR_HIP(rr::launch_queue_reset(a.queue, hs), "queue reset");
   if (t->kind == RR_GRID_UNIFORM) {
     RR_HIP(rr::launch_march_uniform(t->precision, t->data, a, persistent, block, grid_waves, hs),

@@ -1,0 +1,75 @@
+"""Workgroup sizes of launches of few tiles (GPU).
+
+Untuned launches give each wavefront a workgroup of its own up to a number of
+tiles and pack four beyond it.  On both sides of each line (tiles per compute
+unit: 1 for most marches, 3 for FP64 tidal ones, 2 for the adjoint) the map is
+that of either pinned size, bit for bit, and the adjoint is the transpose of the
+march: sum w kappa = sum phi dL/dphi for white noise, within 1e-5 of sum |w kappa|
+(FP32 sums of some 1e6 terms of either sign, each good to about 1e-6).
+"""
+import numpy as np
+import pytest
+
+from paper_1601_02012_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+N = 24
+
+
+@pytest.fixture(scope="module")
+def api():
+    from paper_1601_02012_amd import api as A
+    return A
+
+
+def _bundle(api, tiles):
+    """A map of that many tiles, its last row and column of tiles ragged."""
+    import torch
+    tx = next(x for x in range(int(tiles ** 0.5), 0, -1) if tiles % x == 0)
+    nx, ny = 8 * tx - 3, 8 * (tiles // tx) - 5
+    f = np.radians(4.0)
+    d = torch.as_tensor(I.fov_directions((0.1, -0.05, 1.0), f, f, nx, ny)).cuda()
+    return [api.RayBundle(d, nx, ny, 40.0, 40.0, 0.5)]
+
+
+def _phi(seed=1):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.randn((N, N, N), generator=g, device="cuda")
+
+
+@pytest.mark.parametrize("side", [0, 1])
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("per_cu", [1, 3])
+def test_maps_at_the_lines(api, per_cu, prec, side):
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    v = _phi().to(torch.float32 if prec == "fp32" else torch.float64)
+    t = api.TidalTensor(api.Grid(v, float(N)), prec).build()
+    plan = api.Plan()
+    b = _bundle(api, per_cu * cus + side)
+    got = api.trace(plan, t, b, (0.2, 0.3, 0.4))
+    for block in (64, 256):
+        plan.set_shape(b, block=block)
+        x = api.trace(plan, t, b, (0.2, 0.3, 0.4))
+        assert torch.equal(got.kappa, x.kappa) and torch.equal(got.status, x.status)
+
+
+@pytest.mark.parametrize("side", [0, 1])
+@pytest.mark.parametrize("per_cu", [1, 2])
+def test_adjoint_at_the_lines(api, per_cu, side):
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    phi = _phi(2)
+    grid = api.Grid(phi, float(N))
+    t = api.TidalTensor(grid, "fp32").build()
+    plan = api.Plan()
+    b = _bundle(api, per_cu * cus + side)
+    out = api.trace(plan, t, b, (0.2, 0.3, 0.4), persistent=0)
+    kappa = out.kappa.double() - out.kappa_comp.double()
+    g = torch.Generator(device="cuda").manual_seed(3)
+    w = torch.randn(kappa.numel(), generator=g, device="cuda")
+    grad = api.trace_adjoint(plan, t, grid, b, (0.2, 0.3, 0.4), w)
+    lhs, rhs = (w.double() * kappa), (grad.double() * phi.double())
+    assert abs(float(lhs.sum() - rhs.sum())) <= 1e-5 * float(lhs.abs().sum())
