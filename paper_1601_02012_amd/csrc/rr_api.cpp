@@ -510,16 +510,36 @@ int alone_march(rr_tensor t, int mode) {
 // any more.  The march is bound by its gathers (address unit and L2), so idle
 // lanes cost less than the misses they avoid: 16 bundles of 64^2..384^2 rays over
 // 1..10 degrees through a 96^3 tree of four levels, one persistent launch, 33-42
-// -> 24 ms; 1024^2 rays through a 128^3 tree in the tuner's shape (whose passes
-// split the window in any case) 20.2 -> 18.4 ms.  16 to 72 cells measure alike
-// (24.0-24.7 and 18.0-18.3 ms); at 4 the lanes wait too often (25.1 and 20.3), at
-// 128 they drift (25.8).  With at most two wavefronts per compute unit nothing
-// else fills the machine and the longest wavefront sets the time, so no lane
-// waits: 16 bundles through a 64^3 tree, FP32, 64 tiles 7.35 ms without waiting
-// against 7.85 with, 256 tiles 8.0 against 8.3, 576 tiles 8.3 either way, 1024
-// tiles 9.05 against 8.7, 2304 tiles 10.9 against 9.5.
-double octree_lead(int64_t n_tiles, int cu_count) {
-  return n_tiles <= 2 * (int64_t)cu_count ? INFINITY : 32.0;
+// -> 24 ms; 1024^2 rays through a 128^3 tree 20.2 -> 18.4 ms in the tuner's
+// shape.  16 to 72 cells measure alike (24.0-24.7 and 18.0-18.3 ms); at 4 the
+// lanes wait too often (25.1 and 20.3), at 128 they drift (25.8).
+//
+// Waiting pays where lanes have the way to drift, `span` base cells of chi in one
+// pass; before that its test alone costs up to 12 % (FP32 and FP64, along and off
+// the axes, 256 x 192 to 1024^2 rays; time without waiting over time with):
+//   span              100          200          400          600         1200
+//   tidal direct   0.96 - 1.06  0.97 - 1.12  0.99 - 1.14  1.03 - 1.22  1.11 - 1.42
+//   tidal pers.    0.94 - 1.03  0.94 - 1.04  0.90 - 1.08  1.02 - 1.13  1.13 - 1.34
+//   sources direct 0.97 - 1.04  0.97 - 1.11  0.98 - 1.17  1.05 - 1.27  1.12 - 1.38
+//   sources pers.  0.92 - 1.02  0.88 - 1.01  0.87 - 1.06  0.88 - 1.05  0.96 - 1.14
+//   NGP            0.90 - 0.99  0.91 - 0.99  0.90 - 1.05  0.95 - 1.11  0.98 - 1.19
+// (2300 cells in 16 passes 0.98 - 1.01, in 32 0.96 - 0.99, in 4 1.05 - 1.20, in
+// one 1.14 - 1.64).  With at most two wavefronts per compute unit nothing else
+// fills the machine and the longest wavefront sets the time, so no lane waits: 16
+// bundles through a 64^3 tree, FP32, 64 tiles 7.35 ms without waiting against
+// 7.85 with, 256 tiles 8.0 against 8.3, 576 tiles 8.3 either way, 1024 tiles 9.05
+// against 8.7, 2304 tiles 10.9 against 9.5.
+double octree_lead(int64_t n_tiles, int mode, int persistent, double span, int cu_count) {
+  const double from = mode == 1 || (mode == 3 && persistent) ? 1000.0 : 500.0;
+  return n_tiles <= 2 * (int64_t)cu_count || span < from ? INFINITY : 32.0;
+}
+
+// The longest chi window of the bundles.
+double longest_window(const rr_bundle* b, int32_t nb) {
+  double len = 0.0;
+  for (int32_t i = 0; i < nb; ++i)
+    if (b[i].n_rays > 0) len = std::max(len, b[i].chi_hi - b[i].chi_lo);
+  return len;
 }
 
 // Launch order of the bundles: as given, or (persistent launches)
@@ -1006,7 +1026,6 @@ rr_status launch_trace(rr_plan p, rr_tensor t, const rr_trace_params* tp, const 
     a.pieces = pieces;
   }
   a.queue = p->queue;
-  a.lead = octree_lead(tab->n_tiles, p->cu_count);
   const int grid_waves = p->cu_count * waves_per_cu;
   if (block == 0) block = persistent ? 256 : default_block(a.n_tiles, alone_march(t, a.mode), p->cu_count);
   // A long window can be marched in passes: each pass stops every ray on the
@@ -1043,6 +1062,10 @@ rr_status launch_trace(rr_plan p, rr_tensor t, const rr_trace_params* tp, const 
     RR_HIP(rr::launch_fill(p->resume, nr, INFINITY, hs), "pass state init");
     a.resume = p->resume;
   }
+  a.lead = octree_lead(
+      a.n_tiles, a.mode, persistent,
+      passes > 1 ? (chi_top - chi_bot) / passes : longest_window(bundles, n_bundles) / h0,
+      p->cu_count);
   for (int pass = 0; pass < passes; ++pass) {
     // pass boundaries at equal steps in chi over the bundles' windows; every
     // lane of a wave restarts from the same boundary, so neighbouring rays
@@ -1193,7 +1216,8 @@ rr_status rr_trace_rays_noalloc(rr_tensor t, const rr_trace_params* tp, const rr
   int dev = 0, cus = 0;
   RR_HIP(hipGetDevice(&dev), "hipGetDevice");
   RR_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "CU count");
-  a.lead = octree_lead(tiles, cus);
+  a.lead = octree_lead(tiles, a.mode, persistent,
+                       longest_window(bundles, n_bundles) * t->n / t->box, cus);
   const int grid_waves = cus * 16;
   const int block = persistent ? 256 : default_block(a.n_tiles, alone_march(t, a.mode), cus);
   if (persistent) RR_HIP(rr::launch_queue_reset(a.queue, hs), "queue reset");
