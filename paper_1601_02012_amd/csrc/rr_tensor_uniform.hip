@@ -19,11 +19,11 @@
 // (plus a two-cell halo) in LDS; every thread reads its 4 x 4 patch of that
 // plane once and keeps the per-plane partial stencils of the last four planes
 // in registers, so each vertex costs 16 LDS reads and ~80 arithmetic
-// operations.  Whole-grid builds take 64 x 16 x 16 columns (1024 threads;
-// staging with the halo reads 1.5 potential values per vertex) or 64 x 8 x 32
-// ones and write the records with non-temporal stores (the 3 GiB tensor of a 512^3 grid does not
-// fit any cache); small grids and boxes take columns of 64 x 4 with 256
-// threads (launch_vt) and ordinary stores, since the march reads them right away.
+// operations.  Large grids and boxes take columns of 64 x 8 x 8 (512 threads) or
+// 64 x 16 x 16 (1024 threads; staging with the halo reads 1.5 potential values per
+// vertex) and, beyond the last-level cache, write the records with non-temporal
+// stores; small ones take columns of 64 x 4 with 256 threads and ordinary
+// stores, since the march reads them right away (launch_vt).
 #include "rr_internal.hpp"
 
 namespace rr {
@@ -70,7 +70,7 @@ struct VertexBox {
   int ntx, nty;     // workgroup tiles in x and y
 };
 
-template <typename In, typename Acc, int TY, int KZ, bool kNT>
+template <typename In, typename Acc, int TY, int KZ, bool kNT, bool kRows>
 __global__ __launch_bounds__(64 * TY) void vertex_tensor_uniform_kernel(const In* __restrict__ phi,
                                                                         Acc* __restrict__ tv,
                                                                         int n, int open,
@@ -79,14 +79,13 @@ __global__ __launch_bounds__(64 * TY) void vertex_tensor_uniform_kernel(const In
   constexpr int NT = TX * TY;                 // threads
   constexpr int PX = TX + 3, PY = TY + 3;     // staged plane: halo 2 below, 1 above
   __shared__ Acc plane[2][PY * PX];
-  // Records of whole-grid builds leave through LDS: each wavefront (one row of
-  // 64 vertices) writes its row with contiguous stores instead of three per
-  // lane at the stride of a record.  512^3 FP64: 2.2 -> 1.8 ms, and 1.38 with
-  // the next plane read ahead; FP32 in 64 x 8 columns: 400^3 517 -> 337 us,
-  // 256^3 112 -> 99, 501^3 931 -> 893.  FP32 in 64 x 16 columns (512^3 and up)
-  // keeps per-lane stores: there staging costs the second workgroup per CU.
-  constexpr bool kRowStore = kNT && !(sizeof(Acc) == 4 && TY == 16);
-  __shared__ __align__(16) Acc rowbuf[kRowStore ? TY : 1][kRowStore ? TX * RW : 1];
+  // kRows: records leave through LDS, each wavefront (one row of 64 vertices)
+  // writes its row with contiguous stores instead of three per lane at the stride
+  // of a record.  512^3 FP64: 2.2 -> 1.8 ms, and 1.38 with the next plane read
+  // ahead; 192^3 FP64 0.144 (64 x 4 x 32, per-lane stores) -> 0.073.  FP32 in
+  // 64 x 16 columns keeps per-lane stores: there staging costs the second
+  // workgroup per CU.
+  __shared__ __align__(16) Acc rowbuf[kRows ? TY : 1][kRows ? TX * RW : 1];
 
   const int b = blockIdx.x;
   const int bx = b % V.ntx;
@@ -100,11 +99,13 @@ __global__ __launch_bounds__(64 * TY) void vertex_tensor_uniform_kernel(const In
   i = i >= n ? i - n : i;
   j = j >= n ? j - n : j;
   const int64_t nn = (int64_t)n * n;
-  // the wavefront's row of n_row vertices does not wrap
+  // the wavefront's row of n_row vertices does not wrap (in 64 x 16 columns it is
+  // whole: the rest of an aligned row fills its lines from single lanes, FP64
+  // 480^3 1.143 ms against 1.17)
   int i_row = V.ox + li0;
   i_row = i_row >= n ? i_row - n : i_row;
   const int n_row = min(TX, V.sx - li0);
-  const bool row_ok = kRowStore && i_row + n_row <= n;
+  const bool row_ok = kRows && i_row + n_row <= n && (TY < 16 || n_row == TX);
 
   // per-plane partial stencils, history over planes (index 0 = oldest)
   Acc XX[2], YY[2], XY[2];     // planes k-1, k
@@ -141,7 +142,7 @@ __global__ __launch_bounds__(64 * TY) void vertex_tensor_uniform_kernel(const In
   // with three per-lane stores each (vertex boxes) read each plane when it
   // is staged: there reading ahead was slower (3.3 against 2.2 ms for
   // 512^3); with their rows leaving through LDS it is faster (1.76 -> 1.38).
-  constexpr bool kAhead = sizeof(Acc) == 4 || kRowStore;
+  constexpr bool kAhead = sizeof(Acc) == 4 || kRows;
   In pre[kStage];
   auto fetch = [&](int p, int gzp) {
     const bool zin = p >= 0 && p < n;
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(64 * TY) void vertex_tensor_uniform_kernel(const In
         // start at any multiple of 8 (LDS operations of one wavefront complete
         // in order; the empty asm statements keep the compiler from moving the
         // accesses across each other)
-        Acc* rb = rowbuf[kRowStore ? ty : 0];
+        Acc* rb = rowbuf[kRows ? ty : 0];
         typedef Acc chunk_t __attribute__((ext_vector_type(2)));
         constexpr int kChunks = RW / 2;      // per record
         chunk_t* rc = reinterpret_cast<chunk_t*>(rb);
@@ -237,7 +238,10 @@ __global__ __launch_bounds__(64 * TY) void vertex_tensor_uniform_kernel(const In
             reinterpret_cast<chunk_t*>(tv + ((int64_t)k * nn + (int64_t)j * n + i_row) * RW);
 #pragma unroll
         for (int m = tx; m < TX * kChunks; m += TX)
-          if (m < n_row * kChunks) __builtin_nontemporal_store(rc[m], dst + m);
+          if (m < n_row * kChunks) {
+            if constexpr (kNT) __builtin_nontemporal_store(rc[m], dst + m);
+            else dst[m] = rc[m];
+          }
         __asm__ volatile("" ::: "memory");
       } else if (mine) {
         store_vertex<kNT>(tv + ((int64_t)k * nn + (int64_t)j * n + i) * RW, rec);
@@ -359,7 +363,8 @@ hipError_t launch_ct(int n, int open, const void* phi, void* tc, hipStream_t s) 
   return hipGetLastError();
 }
 
-template <typename In, typename Acc, int TY, int KZ, bool kNT>
+template <typename In, typename Acc, int TY, int KZ, bool kNT,
+          bool kRows = kNT && (sizeof(Acc) == 8 || TY != 16)>
 hipError_t launch_shape(const VertexBox& box, int n, int open, const void* phi, void* tv,
                         hipStream_t s) {
   VertexBox V = box;
@@ -368,7 +373,7 @@ hipError_t launch_shape(const VertexBox& box, int n, int open, const void* phi, 
   const int ntz = (V.sz + KZ - 1) / KZ;
   const int64_t blocks = (int64_t)V.ntx * V.nty * ntz;
   if (blocks == 0) return hipSuccess;
-  hipLaunchKernelGGL((vertex_tensor_uniform_kernel<In, Acc, TY, KZ, kNT>),
+  hipLaunchKernelGGL((vertex_tensor_uniform_kernel<In, Acc, TY, KZ, kNT, kRows>),
                      dim3((unsigned)blocks), dim3(TX * TY), 0, s, (const In*)phi, (Acc*)tv, n,
                      open, V);
   return hipGetLastError();
@@ -385,24 +390,44 @@ hipError_t launch_vt(int n, int open, const int* lo, const int* size, const void
   }
   V.ox = o[0]; V.oy = o[1]; V.oz = o[2];
   V.sx = size[0]; V.sy = size[1]; V.sz = size[2];
-  // Boxes that give the chip fewer than two workgroups per compute unit in the
-  // shapes below take columns of 64 x 4, as deep as leaves it that many: 64^3
-  // FP64 29 -> 10 us, the vertex box of a 512^3 cone's segment 22 -> 8 us.
   auto columns = [&](int ty, int kz) {
     return (int64_t)((V.sx + TX - 1) / TX) * ((V.sy + ty - 1) / ty) * ((V.sz + kz - 1) / kz);
   };
-  constexpr int64_t kFill = 512;
-  // boxes beyond 1/8 of the grid stream through HBM like the whole grid
-  if (8 * (int64_t)V.sx * V.sy * V.sz > (int64_t)n * n * n) {
-    // FP64, and FP32 from 512 a side (where both shapes stream at the memory's
-    // rate: 512^3 0.84 ms against 0.86, 640^3 1.69 against 1.70): 64 x 16 x 16,
-    // the least halo.  Smaller FP32 grids: 64 x 8 x 32 with rows stored through
-    // LDS (figures above).
-    if ((sizeof(Acc) == 8 || n >= 512) && columns(16, 16) >= kFill)
+  // Boxes beyond 1/8 of the grid: rows stored through LDS, in columns of
+  // 64 x 8 x 8 unless said otherwise.  From 128 of those on (72 a side; 64^3 FP64
+  // 13.5 us against 10.2 in 64 x 4 x 4, 80^3 13.7 against 18.7).
+  const int64_t vertices = (int64_t)V.sx * V.sy * V.sz, grid = (int64_t)n * n * n;
+  if (8 * vertices > grid && columns(8, 8) >= 128) {
+    // Records that the last-level cache holds are stored into it: the march reads
+    // them next (128^2 rays after the build, FP32 224^3 160 us against 170 with
+    // non-temporal stores, FP64 128^3 82 against 90; beyond, FP32 250^3 239
+    // against 212, FP64 250^3 322 against 298).
+    if (vertices * 6 * (int64_t)sizeof(Acc) <= (vertices == grid ? 288ll << 20 : 96ll << 20))
+      return launch_shape<In, Acc, 8, 8, false, true>(V, n, open, phi, tv, s);
+    // Whole rows that start on 64-byte lines fill them from any shape: there the
+    // least halo, 64 x 16 x 16, wins on large grids (us, 64 x 16 x 16 / 8 x 8; FP32
+    // / 8 x 32: 384^3 472 / 288 / 304, 400^3 520 / 364 / 322, 408^3 365 / 428 /
+    // 385, 472^3 654 / 795 / 702, 512^3 777 / 950 / 824; FP64 288^3 248 / 243,
+    // 340^3 449 / 499, 512^3 1358 / 1505, 512^2 x 170 439 / 493), except on FP32
+    // slabs (512^2 x 170 373 / 226).  Other rows share their lines, which the
+    // longer bursts of the staged rows mend (FP32 500^3 811 / 739, 510^3 1151 /
+    // 786, 441^3 576 / 545; FP64 333^3 423 / 445, 370^3 573 / 552, 510^3 1570 /
+    // 1404; boxes of 505 x 503 x 256 in 512^3 FP32 688 / 512, FP64 802 / 757).
+    const bool lines = n % (64 / sizeof(Acc) / 2) == 0;
+    if constexpr (sizeof(Acc) == 4) {
+      if (vertices == grid && lines && n > 404)
+        return launch_shape<In, Acc, 16, 16, true>(V, n, open, phi, tv, s);
+      if (vertices == grid && lines && n > 388)
+        return launch_shape<In, Acc, 8, 32, true>(V, n, open, phi, tv, s);
+    } else if (V.sx == n && (lines || n < 352) && columns(16, 16) >= 2048) {
       return launch_shape<In, Acc, 16, 16, true>(V, n, open, phi, tv, s);
-    if constexpr (sizeof(Acc) == 4)
-      if (columns(8, 32) >= kFill) return launch_shape<In, Acc, 8, 32, true>(V, n, open, phi, tv, s);
+    }
+    return launch_shape<In, Acc, 8, 8, true>(V, n, open, phi, tv, s);
   }
+  // Smaller boxes and grids: columns of 64 x 4, as deep as leaves the chip two
+  // workgroups per compute unit: 64^3 FP64 29 -> 10 us, the vertex box of a
+  // 512^3 cone's segment 22 -> 8 us.
+  constexpr int64_t kFill = 512;
   if (columns(4, 32) >= kFill) return launch_shape<In, Acc, 4, 32, false>(V, n, open, phi, tv, s);
   if (columns(4, 8) >= kFill) return launch_shape<In, Acc, 4, 8, false>(V, n, open, phi, tv, s);
   return launch_shape<In, Acc, 4, 4, false>(V, n, open, phi, tv, s);
