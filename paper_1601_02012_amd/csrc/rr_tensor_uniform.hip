@@ -99,13 +99,11 @@ __global__ __launch_bounds__(64 * TY) void vertex_tensor_uniform_kernel(const In
   i = i >= n ? i - n : i;
   j = j >= n ? j - n : j;
   const int64_t nn = (int64_t)n * n;
-  // the wavefront's row of n_row vertices does not wrap (in 64 x 16 columns it is
-  // whole: the rest of an aligned row fills its lines from single lanes, FP64
-  // 480^3 1.143 ms against 1.17)
+  // the wavefront's row of n_row vertices does not wrap
   int i_row = V.ox + li0;
   i_row = i_row >= n ? i_row - n : i_row;
   const int n_row = min(TX, V.sx - li0);
-  const bool row_ok = kRows && i_row + n_row <= n && (TY < 16 || n_row == TX);
+  const bool row_ok = kRows && i_row + n_row <= n;
 
   // per-plane partial stencils, history over planes (index 0 = oldest)
   Acc XX[2], YY[2], XY[2];     // planes k-1, k
