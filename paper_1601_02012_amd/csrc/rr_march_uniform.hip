@@ -863,6 +863,8 @@ __global__ __launch_bounds__(256) void kappa_from_pieces_kernel(const R* __restr
                                                                 const double* __restrict__ src,
                                                                 int ns, int64_t nr,
                                                                 double* __restrict__ kappa) {
+  // two doubles at any address that holds one: all that the caller promises
+  typedef double pair_t __attribute__((ext_vector_type(2), aligned(8)));
   __shared__ double2 pc[256][kPieceTile + 1];
   const int64_t r0 = (int64_t)blockIdx.x * 256;
   const int rays = (int)(nr - r0 < 256 ? nr - r0 : 256);
@@ -884,8 +886,10 @@ __global__ __launch_bounds__(256) void kappa_from_pieces_kernel(const R* __restr
     __syncthreads();
     for (int e = t; e < 256 * kPieceTile; e += 256) {
       const int r = e / kPieceTile, j = j0 + e % kPieceTile;
-      if (r < rays && j < j1)
-        pc[r][e % kPieceTile] = reinterpret_cast<const double2*>(pieces)[(r0 + r) * ns + j];
+      if (r < rays && j < j1) {
+        const pair_t p = *reinterpret_cast<const pair_t*>(pieces + 2 * ((r0 + r) * ns + j));
+        pc[r][e % kPieceTile] = make_double2(p.x, p.y);
+      }
     }
     __syncthreads();
     for (int j = j1 - 1; j >= j0; --j) {
