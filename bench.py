@@ -37,20 +37,37 @@ BYTES_PER_CROSSING = {"fp32": 96, "fp64": 192}     # 4 new corners x 6 component
 # MI355X vector peak: 256 CUs x 4 SIMDs x 32 FP32 lanes x 2 (FMA) x 2.4 GHz;
 # FP64 runs at half that rate
 PEAK_FP32_TFLOPS = 157.3
-# arithmetic of one single-face crossing of the FP32-Kahan march, counted from
-# the method (an FMA counts two): the three-point Gauss integral of the cell
-# (102, scale included), four corner projections P:T (4 x 11), the Kahan
-# update (4) and the local exit coordinates (6) in FP32; the exit selection
-# and tie tests (6 comparisons), exit coordinates (3), the piece length and
-# chi_s - chi_B (2) and the next plane's parameter (2) in FP64
+# arithmetic of one single-face crossing with the three-point Gauss integral,
+# counted from the method (an FMA counts two): the integral of the cell (102,
+# scale included), four corner projections P:T (4 x 11), the Kahan update (4) and
+# the local exit coordinates (6) in FP32; the exit selection and tie tests (6
+# comparisons), exit coordinates (3), the piece length and chi_s - chi_B (2) and
+# the next plane's parameter (2) in FP64.  The octree march evaluates this rule.
 FLOPS_PER_CROSSING = {"fp32": 156, "fp64": 13}
-# arithmetic of one crossing of the adjoint scatter, counted the same way: per
-# Gauss node the node's chi and kernel weight (6), its local coordinates (6),
+# the same for one crossing of a run of the uniform march, which evaluates the
+# piece form: the new face's coefficients (4), the form (dd 3, u1 6, m 13, cA and
+# cB 2), its integral against the kernel (25) with the kernel (1), L^2, the length
+# and the scale in two parts (6), four corner projections (4 x 11), the Kahan
+# update (4) and two exit coordinates (4) in FP32; the exit's test (1), the piece
+# length, chi_s - chi_B and the exit coordinates' distances (4) and the next
+# plane and its parameter (3) in FP64
+RUN_FLOPS_PER_CROSSING = {"fp32": 4 + (3 + 6 + 13 + 2) + (25 + 1) + 6 + 4 * 11 + 4 + 4,
+                          "fp64": 1 + 4 + 3}
+# arithmetic of one general crossing of the adjoint scatter, counted the same way:
+# per Gauss node the node's chi and kernel weight (6), its local coordinates (6),
 # the eight trilinear corner weights scaled by the node weight (3 + 2 + 4 + 8)
 # and their accumulation (8), after the piece's three coordinate differences
 # (3); when a face retires, its four corners' weights times the six projection
 # factors and their sums (24 + 24); the walk's 13 FP64 operations as above
 ADJ_FLOPS_PER_CROSSING = {"fp32": 3 * (6 + 6 + 17 + 8) + 3 + 48, "fp64": 13}
+# and of one crossing of a run of the scatter, the piece form's transpose: the
+# kernel's factors (kernel 1, s, L^2, L and b 6, t 2, k20, k02 and k11 9), the two
+# twist terms (4 + 6) and their eight sums (8), four points added to a face (4 x
+# 10), and the retiring face as above (48) in FP32; the exit's test (1), the piece
+# length and chi_s - chi_B (2), two exit coordinates (4) and the next plane's
+# parameter (2) in FP64
+ADJ_RUN_FLOPS_PER_CROSSING = {"fp32": (1 + 6 + 2 + 9) + (4 + 6) + 8 + 4 * 10 + 48,
+                              "fp64": 1 + 2 + 4 + 2}
 BYTES_PER_VERTEX = {"fp32": 4 + 24, "fp64": 4 + 48}  # potential in, 6 components out
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "march_uniform_lightcone_traffic.md")
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "march_uniform_lightcone_counters.md")
@@ -541,7 +558,7 @@ def adjoint_leg(args, api, I, torch, dev):
     t.close()
     del grad, kap, comp, dphi
     torch.cuda.empty_cache()
-    flops_eq = ADJ_FLOPS_PER_CROSSING["fp32"] + 2 * ADJ_FLOPS_PER_CROSSING["fp64"]
+    flops_eq = ADJ_RUN_FLOPS_PER_CROSSING["fp32"] + 2 * ADJ_RUN_FLOPS_PER_CROSSING["fp64"]
     achieved = flops_eq * cross / (bwd_ms * 1e-3) / 1e12
     # the scatter's atomic bytes from the committed counter summary (same source only)
     prof = profile_figures((ADJOINT_FILE,), ADJOINT_SOURCES, "adjoint_source_sha256_16")
@@ -555,7 +572,7 @@ def adjoint_leg(args, api, I, torch, dev):
             "dot_product_identity_rel_diff": abs(lhs - rhs) / max(abs(lhs), abs(rhs), 1e-300),
             "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS,
                          "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_TFLOPS,
-                         "flops_per_crossing": {**ADJ_FLOPS_PER_CROSSING,
+                         "flops_per_crossing": {**ADJ_RUN_FLOPS_PER_CROSSING,
                                                 "fp32_equivalent": flops_eq},
                          "kernel": "the backward call (scatter_kernel, then transpose_kernel), "
                                    "timed with HIP events on its stream",
@@ -795,7 +812,7 @@ def main():
     march_launch_ms = r32["march_ms"] / nseg
     cross_per_launch = r32["cross"] / nseg
     bytes_gbs = BYTES_PER_CROSSING["fp32"] * cross_per_launch / (march_launch_ms * 1e-3) / 1e9
-    flops_eq = FLOPS_PER_CROSSING["fp32"] + 2 * FLOPS_PER_CROSSING["fp64"]
+    flops_eq = RUN_FLOPS_PER_CROSSING["fp32"] + 2 * RUN_FLOPS_PER_CROSSING["fp64"]
     achieved = flops_eq * cross_per_launch / (march_launch_ms * 1e-3) / 1e12
     prof = profile_figures()
     traffic = prof.get("hbm_bytes_per_launch")
@@ -820,7 +837,8 @@ def main():
                    "chi_s": ctx["chi_s"]},
         "roofline": {"bound": "alu", "achieved": achieved, "peak": PEAK_FP32_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_TFLOPS,
-                     "flops_per_crossing": {**FLOPS_PER_CROSSING, "fp32_equivalent": flops_eq},
+                     "flops_per_crossing": {**RUN_FLOPS_PER_CROSSING,
+                                            "fp32_equivalent": flops_eq},
                      "bytes_model": {"achieved": bytes_gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                                      "frac": bytes_gbs / PEAK_HBM_GBS},
                      "traffic": traffic,
