@@ -487,21 +487,18 @@ rr_status validate_trace(rr_tensor t, const rr_trace_params* tp, const rr_bundle
 // levels), maps along and off the axes over 1.5 and 6 degrees, 256 units:
 //   tiles                  16 - 256     384 - 512     576 - 768    896 - 1024
 //   FP64 tidal           0.98 - 1.26   0.97 - 1.18   0.97 - 1.17   0.95 - 1.05
-//   other uniform        0.96 - 1.08   0.88 - 1.05   0.93 - 1.04   0.94 - 1.06
+//   other trilinear      0.97 - 1.07   0.95 - 1.05   0.95 - 1.04   0.94 - 1.06
+//   NGP                  0.96 - 1.08   0.88 - 1.04   0.93 - 1.04   0.95 - 1.06
 //   octree               1.00 - 1.08   0.93 - 1.04   0.95 - 1.01   0.99 - 1.01
 //   adjoint              1.01 - 1.06   0.98 - 1.06   0.98 - 1.03   0.87 - 1.01
-// The FP64 tidal march (twelve 16-byte loads per crossing and lane) gains up to
-// three per unit along the axes (1.04 to 1.18) and is even off them, the adjoint
-// up to two; the others only lose beyond one.
+// The trilinear marches through uniform grids gain (FP64 along the axes) or are
+// even up to four per unit, and gain 3 to 6 % on ragged maps of 270 to 630 tiles;
+// the adjoint gains up to two; NGP and octree marches only lose beyond one.
 int default_block(int64_t n_tiles, int alone, int cu_count) {
   return n_tiles <= alone * (int64_t)cu_count ? 64 : 256;
 }
 constexpr int kAloneAdjoint = 2;
-int alone_march(rr_tensor t, int mode) {
-  const bool tidal64 = t->kind == RR_GRID_UNIFORM && t->precision == RR_PREC_FP64 &&
-                       (mode == 0 || mode == 3);
-  return tidal64 ? 3 : 1;
-}
+int alone_march(rr_tensor t, int mode) { return t->kind == RR_GRID_UNIFORM && mode != 1 ? 4 : 1; }
 
 // Octree march: how far in chi (base cells) a lane may be ahead of where its
 // wavefront stood when the slowest lane last caught up, before it waits.  A lane

@@ -404,9 +404,10 @@ hipError_t launch_vt(int n, int open, const int* lo, const int* size, const void
       return launch_shape<In, Acc, 8, 8, false, true>(V, n, open, phi, tv, s);
     // Whole rows that start on 64-byte lines fill them from any shape: there the
     // least halo, 64 x 16 x 16, wins on large grids (us, 64 x 16 x 16 / 8 x 8; FP32
-    // / 8 x 32: 384^3 472 / 288 / 304, 400^3 520 / 364 / 322, 408^3 365 / 428 /
-    // 385, 472^3 654 / 795 / 702, 512^3 777 / 950 / 824; FP64 288^3 248 / 243,
-    // 340^3 449 / 499, 512^3 1358 / 1505, 512^2 x 170 439 / 493), except on FP32
+    // / 8 x 32: 320^3 270 / 172 / 179, 336^3 215 / 213 / 199, 384^3 472 / 288 /
+    // 304, 400^3 520 / 364 / 322, 408^3 365 / 428 / 385, 472^3 654 / 795 / 702,
+    // 512^3 777 / 950 / 824; FP64 288^3 248 / 243, 340^3 449 / 499, 512^3 1358 /
+    // 1505, 512^2 x 170 439 / 493), except on FP32
     // slabs (512^2 x 170 373 / 226).  Other rows share their lines, which the
     // longer bursts of the staged rows mend (FP32 500^3 811 / 739, 510^3 1151 /
     // 786, 441^3 576 / 545; FP64 333^3 423 / 445, 370^3 573 / 552, 510^3 1570 /
@@ -415,7 +416,7 @@ hipError_t launch_vt(int n, int open, const int* lo, const int* size, const void
     if constexpr (sizeof(Acc) == 4) {
       if (vertices == grid && lines && n > 404)
         return launch_shape<In, Acc, 16, 16, true>(V, n, open, phi, tv, s);
-      if (vertices == grid && lines && n > 388)
+      if (vertices == grid && lines && n > 320)
         return launch_shape<In, Acc, 8, 32, true>(V, n, open, phi, tv, s);
     } else if (V.sx == n && (lines || n < 352) && columns(16, 16) >= 2048) {
       return launch_shape<In, Acc, 16, 16, true>(V, n, open, phi, tv, s);

@@ -2,8 +2,8 @@
 
 Untuned launches give each wavefront a workgroup of its own up to a number of
 tiles and pack four beyond it.  On both sides of each line (tiles per compute
-unit: 1 for most marches, 3 for FP64 tidal ones, 2 for the adjoint) the map is
-that of either pinned size, bit for bit, and the adjoint is the transpose of the
+unit: 4 for trilinear marches, 1 for NGP ones, 2 for the adjoint) the map is that
+of either pinned size, bit for bit, and the adjoint is the transpose of the
 march: sum w kappa = sum phi dL/dphi for white noise, within 1e-5 of sum |w kappa|
 (FP32 sums of some 1e6 terms of either sign, each good to about 1e-6).
 """
@@ -41,18 +41,19 @@ def _phi(seed=1):
 
 @pytest.mark.parametrize("side", [0, 1])
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
-@pytest.mark.parametrize("per_cu", [1, 3])
-def test_maps_at_the_lines(api, per_cu, prec, side):
+@pytest.mark.parametrize("per_cu,integral", [(1, "ngp"), (4, "trilinear")])
+def test_maps_at_the_lines(api, per_cu, integral, prec, side):
     import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     v = _phi().to(torch.float32 if prec == "fp32" else torch.float64)
-    t = api.TidalTensor(api.Grid(v, float(N)), prec).build()
+    t = api.TidalTensor(api.Grid(v, float(N)), prec)
+    t.build_centres() if integral == "ngp" else t.build()
     plan = api.Plan()
     b = _bundle(api, per_cu * cus + side)
-    got = api.trace(plan, t, b, (0.2, 0.3, 0.4))
+    got = api.trace(plan, t, b, (0.2, 0.3, 0.4), integral=integral)
     for block in (64, 256):
         plan.set_shape(b, block=block)
-        x = api.trace(plan, t, b, (0.2, 0.3, 0.4))
+        x = api.trace(plan, t, b, (0.2, 0.3, 0.4), integral=integral)
         assert torch.equal(got.kappa, x.kappa) and torch.equal(got.status, x.status)
 
 
