@@ -392,26 +392,31 @@ hipError_t launch_vt(int n, int open, const int* lo, const int* size, const void
     return (int64_t)((V.sx + TX - 1) / TX) * ((V.sy + ty - 1) / ty) * ((V.sz + kz - 1) / kz);
   };
   // Boxes beyond 1/8 of the grid: rows stored through LDS, in columns of
-  // 64 x 8 x 8 unless said otherwise.  From 128 of those on (72 a side; 64^3 FP64
-  // 13.5 us against 10.2 in 64 x 4 x 4, 80^3 13.7 against 18.7).
+  // 64 x 8 x 8 unless said otherwise.  They want enough columns (us, in 64 x 4 /
+  // 64 x 8 x 8 columns): FP64 64^3, 64 columns, 10.2 / 13.5, 80^3, 200, 18.7 / 13.7;
+  // FP32 128^3, 512, 17.0 / 14.7 but even or 1 to 3 % behind in a step of build and
+  // march up to 136^3, 867; 160^3, 1200, 31.1 / 29.4; FP32 boxes 125^2 x 250, 1024,
+  // 27.6 / 35.2, 144^2 x 288, 1944, 45 / 51, 166^2 x 333, 2646, 79 / 72.
   const int64_t vertices = (int64_t)V.sx * V.sy * V.sz, grid = (int64_t)n * n * n;
-  if (8 * vertices > grid && columns(8, 8) >= 128) {
-    // Records that the last-level cache holds are stored into it: the march reads
-    // them next (128^2 rays after the build, FP32 224^3 160 us against 170 with
-    // non-temporal stores, FP64 128^3 82 against 90; beyond, FP32 250^3 239
-    // against 212, FP64 250^3 322 against 298).
-    if (vertices * 6 * (int64_t)sizeof(Acc) <= (vertices == grid ? 288ll << 20 : 96ll << 20))
+  const int64_t rows_from = sizeof(Acc) == 8 ? 128 : (vertices == grid ? 900 : 2200);
+  if (8 * vertices > grid && columns(8, 8) >= rows_from) {
+    // Records that the last-level cache holds beside the rest of a step are stored
+    // into it: the march reads them next.  Whole steps of drawn maps, time of a
+    // limit of 96 MiB over one of 160, and of 160 over 288: FP32 tensors of 96 to
+    // 160 MiB 1.03, 160 to 224 MiB 0.97 (0.91 at worst), 224 to 288 MiB 0.98; FP64
+    // 1.05 and 1.02.
+    if (vertices * 6 * (int64_t)sizeof(Acc) <= (vertices == grid ? 160ll << 20 : 96ll << 20))
       return launch_shape<In, Acc, 8, 8, false, true>(V, n, open, phi, tv, s);
     // Whole rows that start on 64-byte lines fill them from any shape: there the
     // least halo, 64 x 16 x 16, wins on large grids (us, 64 x 16 x 16 / 8 x 8; FP32
     // / 8 x 32: 320^3 270 / 172 / 179, 336^3 215 / 213 / 199, 384^3 472 / 288 /
     // 304, 400^3 520 / 364 / 322, 408^3 365 / 428 / 385, 472^3 654 / 795 / 702,
     // 512^3 777 / 950 / 824; FP64 288^3 248 / 243, 340^3 449 / 499, 512^3 1358 /
-    // 1505, 512^2 x 170 439 / 493), except on FP32
-    // slabs (512^2 x 170 373 / 226).  Other rows share their lines, which the
-    // longer bursts of the staged rows mend (FP32 500^3 811 / 739, 510^3 1151 /
-    // 786, 441^3 576 / 545; FP64 333^3 423 / 445, 370^3 573 / 552, 510^3 1570 /
-    // 1404; boxes of 505 x 503 x 256 in 512^3 FP32 688 / 512, FP64 802 / 757).
+    // 1505, 512^2 x 170 439 / 493), except on FP32 slabs (512^2 x 170 373 / 226).
+    // Other rows share their lines, which the longer bursts of the staged rows mend
+    // (FP32 500^3 811 / 739, 510^3 1151 / 786, 441^3 576 / 545; FP64 333^3 423 /
+    // 445, 370^3 573 / 552, 510^3 1570 / 1404; boxes of 505 x 503 x 256 in 512^3
+    // FP32 688 / 512, FP64 802 / 757).
     const bool lines = n % (64 / sizeof(Acc) / 2) == 0;
     if constexpr (sizeof(Acc) == 4) {
       if (vertices == grid && lines && n > 404)

@@ -22,10 +22,11 @@ def api():
     return A
 
 
-# columns of 64 x 8 x 8: 72 -> 162; records beyond 288 MiB: FP32 from 233, FP64 from
-# 185; 64-byte lines of rows: FP32 n % 8, FP64 n % 4
-@pytest.mark.parametrize("n,prec", [(71, "fp32"), (73, "fp64"), (74, "fp32"),   # 64 x 8 x 8
-                                    (180, "fp64"), (190, "fp64"), (237, "fp32"),
+# columns of 64 x 8 x 8: FP64 from 65 a side, FP32 from 137; records beyond 160 MiB:
+# FP64 from 152, FP32 from 192; 64-byte lines of rows: FP32 n % 8, FP64 n % 4
+@pytest.mark.parametrize("n,prec", [(64, "fp64"), (65, "fp64"), (73, "fp64"),   # 64 x 8 x 8
+                                    (135, "fp32"), (139, "fp32"), (150, "fp64"),
+                                    (155, "fp64"), (197, "fp32"), (237, "fp32"),
                                     (340, "fp64"), (335, "fp64"),               # 64 x 16 x 16
                                     (354, "fp64"),                              # 64 x 8 x 8
                                     (321, "fp32"), (328, "fp32"), (392, "fp32"),   # 8, 8 x 32
@@ -39,6 +40,7 @@ def test_whole_grids(api, n, prec):
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
 @pytest.mark.parametrize("n,lo,size", [
     (120, (2, 0, 7), (100, 75, 91)), (120, (47, -5, 118), (95, 88, 77)),   # into the cache
+    (173, (101, 3, -9), (153, 150, 141)),
     (230, (6, 3, 0), (201, 190, 180)), (230, (-7, 100, 200), (210, 165, 171)),  # past it
     (230, (173, 0, 5), (229, 230, 97)),
     (360, (0, 11, -3), (360, 350, 98))])                                   # slab of whole rows
