@@ -127,7 +127,7 @@ __device__ __forceinline__ void load_face(const R* __restrict__ tv, Off w0, Off 
 // of the quad has loaded the record of corner i, and v_mfma_f32_4x4x1_16b
 // (sixteen 4 x 4 outer products, one per quad) accumulates over the
 // components f[i] = sum_c T_c(lane i) P_c(own lane): the rounding of the fma
-// chain in corner_value, component by component, with a quarter of its loads.
+// chain in record_value, component by component, with a quarter of its loads.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 template <int kMode>
 __device__ __forceinline__ void project_quad(const float* t, const float* P, float* f,
@@ -795,7 +795,8 @@ __device__ __forceinline__ void run_tile(const R* __restrict__ tv, const TraceAr
 // under that cap; FP64 takes what it needs (three: 32 registers spilled, 24.0
 // against 16.0 ms for five 512^3 segments).  Five (96 VGPRs, 14 spilled) gained
 // nothing: 0.95 against 0.89 ms per 512^3 segment of 2048^2 rays; Method A,
-// which spills 8 at four, took 8.4 ms for five segments against 8.8 at three
+// which spills at four (4 registers in a direct launch, 12 in a persistent one, 8
+// in the direct one timed), took 8.4 ms for five segments against 8.8 at three
 // (both pairs timed before the re-alignment of lanes a layer apart).  Without
 // runs: four as well, and what they need for the others (FP32 at five 0.6 of the
 // speed, FP64 at three 0.8 to 1).
