@@ -395,10 +395,11 @@ hipError_t launch_vt(int n, int open, const int* lo, const int* size, const void
   // 64 x 8 x 8 unless said otherwise.  They want enough columns (us, in 64 x 4 /
   // 64 x 8 x 8 columns): FP64 64^3, 64 columns, 10.2 / 13.5, 80^3, 200, 18.7 / 13.7;
   // FP32 128^3, 512, 17.0 / 14.7 but even or 1 to 3 % behind in a step of build and
-  // march up to 136^3, 867; 160^3, 1200, 31.1 / 29.4; FP32 boxes 125^2 x 250, 1024,
+  // march up to 136^3, 867; 144^3, 972, 27.7 / 30.7 with another potential each
+  // time; 160^3, 1200, 31.1 / 29.4; FP32 boxes 125^2 x 250, 1024,
   // 27.6 / 35.2, 144^2 x 288, 1944, 45 / 51, 166^2 x 333, 2646, 79 / 72.
   const int64_t vertices = (int64_t)V.sx * V.sy * V.sz, grid = (int64_t)n * n * n;
-  const int64_t rows_from = sizeof(Acc) == 8 ? 128 : (vertices == grid ? 900 : 2200);
+  const int64_t rows_from = sizeof(Acc) == 8 ? 128 : (vertices == grid ? 1000 : 2200);
   if (8 * vertices > grid && columns(8, 8) >= rows_from) {
     // Records that the last-level cache holds beside the rest of a step are stored
     // into it: the march reads them next.  Whole steps of drawn maps, time of a
@@ -408,22 +409,20 @@ hipError_t launch_vt(int n, int open, const int* lo, const int* size, const void
     if (vertices * 6 * (int64_t)sizeof(Acc) <= (vertices == grid ? 160ll << 20 : 96ll << 20))
       return launch_shape<In, Acc, 8, 8, false, true>(V, n, open, phi, tv, s);
     // Whole rows that start on 64-byte lines fill them from any shape: there the
-    // least halo, 64 x 16 x 16, wins on large grids (us, 64 x 16 x 16 / 8 x 8; FP32
-    // / 8 x 32: 320^3 270 / 172 / 179, 336^3 215 / 213 / 199, 384^3 472 / 288 /
-    // 304, 400^3 520 / 364 / 322, 408^3 365 / 428 / 385, 472^3 654 / 795 / 702,
-    // 512^3 777 / 950 / 824; FP64 288^3 248 / 243, 340^3 449 / 499, 512^3 1358 /
-    // 1505, 512^2 x 170 439 / 493), except on FP32 slabs (512^2 x 170 373 / 226).
-    // Other rows share their lines, which the longer bursts of the staged rows mend
-    // (FP32 500^3 811 / 739, 510^3 1151 / 786, 441^3 576 / 545; FP64 333^3 423 /
-    // 445, 370^3 573 / 552, 510^3 1570 / 1404; boxes of 505 x 503 x 256 in 512^3
-    // FP32 688 / 512, FP64 802 / 757).
+    // least halo, 64 x 16 x 16, wins on large grids (us, 64 x 16 x 16 / 8 x 8, each
+    // build of another potential; FP32 240^3 102 / 101, 256^3 103 / 114, 288^3 152 /
+    // 170, 328^3 225 / 277, 400^3 396 / 468, 480^3 665 / 809; FP64 176^3 71 / 67,
+    // 208^3 117 / 123, 256^3 166 / 183, 320^3 330 / 368, 480^3 1177 / 1310, slabs of
+    // 512^2 x 170 439 / 493), except on FP32 slabs (512^2 x 170 373 / 226).  Other
+    // rows share their lines, which the longer bursts of the staged rows mend
+    // (FP32 257^3 130 / 113, 333^3 258 / 242, 441^3 567 / 557, 500^3 805 / 741;
+    // FP64 257^3 204 / 197, 333^3 423 / 417, 441^3 1025 / 968; boxes of 493 x 491 x
+    // 250 in 500^3 FP32 542 / 372, FP64 795 / 758).
     const bool lines = n % (64 / sizeof(Acc) / 2) == 0;
     if constexpr (sizeof(Acc) == 4) {
-      if (vertices == grid && lines && n > 404)
+      if (lines && vertices == grid && n >= 250)
         return launch_shape<In, Acc, 16, 16, true>(V, n, open, phi, tv, s);
-      if (vertices == grid && lines && n > 320)
-        return launch_shape<In, Acc, 8, 32, true>(V, n, open, phi, tv, s);
-    } else if (V.sx == n && (lines || n < 352) && columns(16, 16) >= 2048) {
+    } else if (lines && (vertices == grid ? n >= 190 : V.sx == n && columns(16, 16) >= 2048)) {
       return launch_shape<In, Acc, 16, 16, true>(V, n, open, phi, tv, s);
     }
     return launch_shape<In, Acc, 8, 8, true>(V, n, open, phi, tv, s);

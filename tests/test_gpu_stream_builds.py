@@ -1,8 +1,8 @@
 """Vertex tensors and boxes whose rows are stored through LDS (GPU).
 
 Each shape of launch_vt beyond the small columns, with remainders on every axis:
-64 x 8 x 8 into the cache and past it, 64 x 8 x 32 and, in FP32, 64 x 16 x 16 with
-per-lane stores, on whole grids; on boxes above 1/8 of the grid with even, odd and
+64 x 8 x 8 into the cache and past it and 64 x 16 x 16 (FP32 with per-lane stores),
+on whole grids; on boxes above 1/8 of the grid with even, odd and
 wrapping origins, whose rows then start off the lines or wrap (per-lane stores),
 and slabs of whole rows.  The vertices outside a box stay as they were.
 Reference and tolerance: those of the ragged grids (FP64 torch; 1e-12 of the
@@ -22,15 +22,16 @@ def api():
     return A
 
 
-# columns of 64 x 8 x 8: FP64 from 65 a side, FP32 from 137; records beyond 160 MiB:
-# FP64 from 152, FP32 from 192; 64-byte lines of rows: FP32 n % 8, FP64 n % 4
-@pytest.mark.parametrize("n,prec", [(64, "fp64"), (65, "fp64"), (73, "fp64"),   # 64 x 8 x 8
-                                    (135, "fp32"), (139, "fp32"), (150, "fp64"),
-                                    (155, "fp64"), (197, "fp32"), (237, "fp32"),
-                                    (340, "fp64"), (335, "fp64"),               # 64 x 16 x 16
-                                    (354, "fp64"),                              # 64 x 8 x 8
-                                    (321, "fp32"), (328, "fp32"), (392, "fp32"),   # 8, 8 x 32
-                                    (408, "fp32"), (410, "fp32")])              # 16 x 16, 8 x 8
+# 64 x 8 x 8: FP64 from 65 a side, FP32 from 145; records beyond 160 MiB: FP64 from
+# 152, FP32 from 192; 64 x 16 x 16: rows on 64-byte lines (FP32 n % 8, FP64 n % 4),
+# FP32 from 250, FP64 from 190
+@pytest.mark.parametrize("n,prec", [(64, "fp64"), (65, "fp64"), (73, "fp64"), (144, "fp32"),
+                                    (145, "fp32"), (150, "fp64"), (155, "fp64"),
+                                    (188, "fp64"), (190, "fp64"), (191, "fp64"),
+                                    (197, "fp32"), (237, "fp32"), (248, "fp32"),
+                                    (252, "fp64"), (264, "fp32"), (257, "fp32"),
+                                    (335, "fp64"), (340, "fp64"), (408, "fp32"),
+                                    (410, "fp32")])
 def test_whole_grids(api, n, prec):
     p = _field(n, prec)
     t = api.TidalTensor(api.Grid(p, 1.0), prec)
